@@ -19,7 +19,7 @@ ROOT = os.path.dirname(HERE)
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(HERE, "libchfsi.so")
 
-SOURCES = ["gemm.hip", "blas1.hip", "dense_small.hip", "stencil.hip", "complex.hip", "bloch.hip",
+SOURCES = ["gemm.hip", "gemm_split.hip", "blas1.hip", "dense_small.hip", "stencil.hip", "complex.hip", "bloch.hip",
            "noalloc.hip", "lanczos.hip", "csr.hip", "chfsi.cpp", "server.cpp"]
 # Packed FP32 VALU instructions are disabled for every HIP compile.
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",

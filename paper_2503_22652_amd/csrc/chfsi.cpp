@@ -125,14 +125,14 @@ struct chfsi_ctx {
   const Allocator* al = nullptr;   // memory source (null: hipMalloc / hipHostMalloc)
 
   // filter precision copies / buffers
-  float* A32 = nullptr;
-  uint16_t* A16 = nullptr;        // bfloat16 copy of a dense operator (BF16 residual filter)
+  void* A32 = nullptr;            // packed FP32 copy of a dense operator (FP32 filters)
+  void* A16 = nullptr;            // packed bfloat16 copy (BF16 residual filter)
   float* dinv32 = nullptr;        // FP32 D^{-1} (dense: always; stencil: only when given)
   float* Vf = nullptr;            // FP32 potential of a stencil operator (FP32/BF16 filter)
   double* Ht = nullptr;           // exact-inverse filter operator, stored as H^T = A B^{-1} (n x n)
   // complex Hermitian operator (residual filter only): planar left operand
-  // L = [A_r | A_i] (n x 2n, filter precision), [d; d], the materialised right
-  // operand Z~ (2n x 2b, FP32/FP64) and its bfloat16 copy (BF16)
+  // L = [A_r | A_i] (n x 2n, filter precision; FP32/BF16: packed), [d; d] and
+  // the materialised right operand Z~ (2n x 2b, FP64)
   bool cplx = false;
   bool bloch = false;             // Bloch-phase grid operator (twisted frame, planar blocks)
   void* bcorr = nullptr;          // its filter step's boundary correction (nbnd x 2b)
@@ -408,11 +408,12 @@ SizePlan plan_sizes_complex(const chfsi_operator* A, const chfsi_params* p) {
   SizePlan s;
   const int64_t n = A->n, b = p->block;
   const size_t el = p->filter_prec == CHFSI_PREC_FP64 ? sizeof(double) : sizeof(float);
-  const size_t lel = p->filter_prec == CHFSI_PREC_BF16 ? sizeof(uint16_t) : el;
-  s.a32 = size_t(n) * 2 * n * lel + size_t(2) * n * el;              // L, [d; d]
+  const bool f64 = p->filter_prec == CHFSI_PREC_FP64;
+  const int planes = p->filter_prec == CHFSI_PREC_BF16 ? 1 : 3;
+  s.a32 = (f64 ? size_t(n) * 2 * n * el : filter_operator_bytes(n, 2, planes)) +   // L
+          size_t(2) * n * el;                                          // [d; d]
   s.f32blk = size_t(n) * 2 * b * el;                                   // one planar block
-  size_t zt = size_t(2) * n * 2 * b * el;                              // Z~
-  if (p->filter_prec == CHFSI_PREC_BF16) zt += size_t(2) * n * 2 * b * sizeof(uint16_t);
+  const size_t zt = f64 ? size_t(2) * n * 2 * b * el : 0;              // Z~
   s.coef = size_t(p->degree + 1) * 2 * b * sizeof(double);
   // Rayleigh-Ritz on the 2b x 2b real embedding
   const int64_t m = 2 * b;
@@ -424,10 +425,10 @@ SizePlan plan_sizes_complex(const chfsi_operator* A, const chfsi_params* p) {
               size_t(n) * 2 * n * sizeof(double) +                     // LA64 (FP32/BF16), LB64
               5 * s.blk + size_t(2) * n * 2 * b * sizeof(double) +     // planar blocks, Y~
               3 * s.blk + 12 * s.bb + 8 * m * sizeof(double);         // Xw, Yw, R, small
-  size_t ws = p->filter_prec == CHFSI_PREC_FP64
-                  ? std::max(plan_bytes<double>(n, 2 * b, 2 * n), size_t(16) * n * 2 * b * el)
-                  : std::max(plan_bytes<float>(n, 2 * b, 2 * n), size_t(16) * n * 2 * b * el);
-  if (p->filter_prec == CHFSI_PREC_BF16) ws = std::max(ws, gemm_bf16_workspace_bytes(n, 2 * b));
+  // the filter's packed operands and split-K partials
+  size_t ws = std::max(size_t(16) * n * 2 * b * el,
+                       f64 ? plan_bytes<double>(n, 2 * b, 2 * n)
+                           : filter_product_bytes(n, 2 * b, 2, planes));
   ws = std::max(ws, plan_bytes<double>(n, m, 2 * n));
   ws = std::max(ws, plan_bytes<double>(m, m, n));
   ws = std::max(ws, 2 * gemm_workspace_bytes(b, b, n, sizeof(double)));   // batched Gram blocks
@@ -506,11 +507,11 @@ SizePlan plan_sizes_kind(const chfsi_operator* A, const chfsi_operator* B, const
   s.bb = size_t(b) * b * sizeof(double);
   if (p->filter_prec == CHFSI_PREC_FP32) {
     s.f32blk = size_t(n) * b * sizeof(float);
-    if (dense) s.a32 = size_t(n) * n * sizeof(float) + size_t(n) * sizeof(float);
+    if (dense) s.a32 = filter_operator_bytes(n, 1, 3) + size_t(n) * sizeof(float);
   } else if (p->filter_prec == CHFSI_PREC_BF16 && dense) {
     // BF16 products on a bfloat16 copy of A, FP32 filter blocks
     s.f32blk = size_t(n) * b * sizeof(float);
-    s.a32 = size_t(n) * n * sizeof(uint16_t) + size_t(n) * sizeof(float) + size_t(n) * b * 2;
+    s.a32 = filter_operator_bytes(n, 1, 1) + size_t(n) * sizeof(float);
   } else if (p->filter_prec == CHFSI_PREC_FP64) {
     s.f64blk = s.blk;
   } else if (p->escalate) {
@@ -518,7 +519,7 @@ SizePlan plan_sizes_kind(const chfsi_operator* A, const chfsi_operator* B, const
   } else {
     s.bfblk = size_t(n) * b * 2;
   }
-  if (p->escalate && dense) s.a32 += size_t(n) * n * sizeof(float);   // FP32 copy of A
+  if (p->escalate && dense) s.a32 += filter_operator_bytes(n, 1, 3);   // FP32 copy of A
   // stencil filters in FP32/BF16: FP32 copies of D^{-1} and of the potential
   if (A->kind == CHFSI_OP_STENCIL27 && p->filter_prec != CHFSI_PREC_FP64)
     s.a32 += size_t(n) * sizeof(float) * (1 + (A->field_mode != 0 ? 1 : 0));
@@ -528,13 +529,15 @@ SizePlan plan_sizes_kind(const chfsi_operator* A, const chfsi_operator* B, const
   s.coef = size_t(p->degree + 1) * b * sizeof(double);
   size_t ws = 0;
   if (dense) {
-    // the filter product may be run with up to 16 k-splits (tuning knob)
-    if (p->filter_prec == CHFSI_PREC_FP32)
-      ws = std::max(ws, std::max(plan_bytes<float>(n, b, n), size_t(16) * n * b * sizeof(float)));
+    // the filter product may be run with up to 16 k-splits (tuning knob; FP32 and
+    // BF16: the packed right operand takes a part)
     ws = std::max(ws, plan_bytes<double>(n, b, n));
     if (p->filter_prec == CHFSI_PREC_FP64)
       ws = std::max(ws, size_t(16) * n * b * sizeof(double));
-    if (p->filter_prec == CHFSI_PREC_BF16) ws = std::max(ws, gemm_bf16_workspace_bytes(n, b));
+    else
+      ws = std::max(ws, std::max(size_t(16) * n * b * sizeof(float),
+                                 filter_product_bytes(n, b, 1, p->filter_prec == CHFSI_PREC_FP32 ||
+                                                                       p->escalate ? 3 : 1)));
   }
   ws = std::max(ws, plan_bytes<double>(b, b, n));
   ws = std::max(ws, plan_bytes<double>(n, b, b));
@@ -683,6 +686,17 @@ hipError_t prof_pair(chfsi_ctx* c, hipEvent_t* b, hipEvent_t* e) {
   return hipSuccess;
 }
 
+// One dense FP32 / BF16 filter product (profiled as a whole: packing, product
+// and the reduction that carries the epilogue).
+chfsi_status dense_product(chfsi_ctx* c, const FilterProduct& d, int* packed) {
+  hipEvent_t e0, e1;
+  CK(prof_pair(c, &e0, &e1));
+  if (e0) CK(hipEventRecord(e0, c->stream));
+  CK(filter_product(d, c->stream, c->ws, -1, filter_gemm_splits(), packed));
+  if (e1) CK(hipEventRecord(e1, c->stream));
+  return CHFSI_OK;
+}
+
 chfsi_status ensure_coef(chfsi_ctx* c, int p) {
   if (p <= c->coef_cap) return CHFSI_OK;
   set_error("degree %d exceeds the context's degree %d", p, c->coef_cap);
@@ -736,24 +750,22 @@ chfsi_status filter_rchfsi(chfsi_ctx* c, const double* X, int64_t ldx, const dou
     float* RY = c->f32_b;
     float* Yc = c->f32_c;
     CK(rchfsi_init_f32(resid, ldr, n, b, scale1, RY, RX, Yc, n, c->stream));
-    // dense BF16: each step's split-K reduction also rounds D^{-1} R_Y for the next
-    bool b16_ready = false;
+    int packed = 0;   // dense: each step leaves the next one's right operand in the workspace
     for (int s = 0; s < nsteps; ++s) {
       const StepCoef sp = next_step();
       if (dense) {
-        GemmDesc<float> g;
-        g.M = n;
+        const bool bf = c->prm.filter_prec == CHFSI_PREC_BF16;
+        FilterProduct g;
+        g.planes = bf ? 1 : 3;
+        g.A = bf ? static_cast<const void*>(c->A16) : c->A32;
+        g.n = n;
         g.N = b;
-        g.K = n;
-        g.A = c->A32;
-        g.sak = 1;
-        g.sam = n;
         g.B = RY;
-        g.sbk = 1;
-        g.sbn = n;
+        g.ldb = n;
         g.kscale = c->dinv32;
         g.C = RX;
         g.ldc = n;
+        g.pack_next = s + 1 < nsteps;
         g.epi.alpha = float(sp.a);
         g.epi.beta = float(sp.bb);
         g.epi.C1 = RY;
@@ -765,16 +777,8 @@ chfsi_status filter_rchfsi(chfsi_ctx* c, const double* X, int64_t ldx, const dou
         g.epi.colscale3 = c->coef32 + int64_t(s) * b;
         g.epi.C3 = Yc;
         g.epi.ldc3 = n;
-        CK(prof_pair(c, &g.ev_begin, &g.ev_end));
-        if (c->prm.filter_prec == CHFSI_PREC_BF16) {
-          uint16_t* b16 = static_cast<uint16_t*>(c->bf_a);
-          bool next_ready = false;
-          CK(gemm_bf16_filter(g, c->A16, n, b16, c->stream, c->ws, filter_gemm_splits(),
-                              b16_ready, s + 1 < nsteps ? b16 : nullptr, c->dinv32,
-                              &next_ready));
-          b16_ready = next_ready;
-        } else
-          CK(gemm<float>(g, c->stream, c->ws, filter_gemm_splits(), filter_gemm_cfg()));
+        st = dense_product(c, g, &packed);
+        if (st != CHFSI_OK) return st;
         fl += 2.0 * double(n) * double(n) * double(b);
       } else {
         StencilStep ss{sp.a, sp.bb, sp.cc, sp.a};
@@ -1061,7 +1065,7 @@ chfsi_status filter_rchfsi_complex(chfsi_ctx* c, const double* X, int64_t ldx, c
     }
     CK(cplx_reconstruct<double>(RY, c->dinv, X, ldx, c->lamY, Yp, ldy, n, b, c->stream));
   } else {
-    // FP32 blocks; FP32 MFMA on the FP32 L, or bfloat16 MFMA on the bfloat16 L
+    // FP32 blocks; the product on the FP32 or the bfloat16 copy of [A_r | A_i]
     if (nsteps > 0) {
       float* hs = reinterpret_cast<float*>(static_cast<char*>(c->h_stage) + b * sizeof(double));
       std::memcpy(hs, c->h_coef32.data(), size_t(nsteps) * b2 * sizeof(float));
@@ -1071,26 +1075,24 @@ chfsi_status filter_rchfsi_complex(chfsi_ctx* c, const double* X, int64_t ldx, c
     float* RX = c->f32_a;
     float* RY = c->f32_b;
     float* Yc = c->f32_c;
-    float* Zt = static_cast<float*>(c->Zt);
+    int packed = 0;
     const bool bf = c->prm.filter_prec == CHFSI_PREC_BF16;
     CK(hipEventRecord(c->ev_stage, c->stream));
     CK(cplx_init<float>(resid, ldr, n, b, scale1, RY, RX, Yc, c->stream));
     for (int s = 0; s < nsteps; ++s) {
       const Step& sp = steps[s];
-      CK(cplx_rhs<float>(RY, n, b, Zt, c->stream));
-      GemmDesc<float> g;
-      g.M = n;
+      FilterProduct g;
+      g.planes = bf ? 1 : 3;
+      g.nseg = 2;
+      g.A = c->Lc;
+      g.n = n;
       g.N = b2;
-      g.K = 2 * n;
-      g.A = bf ? nullptr : static_cast<const float*>(c->Lc);
-      g.sak = 1;
-      g.sam = 2 * n;
-      g.B = Zt;
-      g.sbk = 1;
-      g.sbn = 2 * n;
+      g.B = RY;
+      g.ldb = n;
       g.kscale = static_cast<const float*>(c->dinv2);
       g.C = RX;
       g.ldc = n;
+      g.pack_next = s + 1 < nsteps;
       g.epi.alpha = float(sp.a);
       g.epi.beta = float(sp.bb);
       g.epi.C1 = RY;
@@ -1102,14 +1104,8 @@ chfsi_status filter_rchfsi_complex(chfsi_ctx* c, const double* X, int64_t ldx, c
       g.epi.colscale3 = c->coef32 + int64_t(s) * b2;
       g.epi.C3 = Yc;
       g.epi.ldc3 = n;
-      CK(prof_pair(c, &g.ev_begin, &g.ev_end));
-      if (bf) {
-        uint16_t* Zt16 = reinterpret_cast<uint16_t*>(Zt + size_t(2) * n * b2);
-        CK(gemm_bf16_filter(g, static_cast<const uint16_t*>(c->Lc), 2 * n, Zt16, c->stream, c->ws,
-                            filter_gemm_splits()));
-      } else {
-        CK(gemm<float>(g, c->stream, c->ws, filter_gemm_splits(), filter_gemm_cfg()));
-      }
+      st = dense_product(c, g, &packed);
+      if (st != CHFSI_OK) return st;
       fl += 8.0 * double(n) * double(n) * double(b);
       std::swap(RX, RY);
     }
@@ -1204,20 +1200,18 @@ chfsi_status filter_chfsi(chfsi_ctx* c, const double* X, int64_t ldx, double* Yp
     float* nxt = c->f32_b;
     CK(convert_f64_f32(X, ldx, Xc, n, n, b, c->stream));
     const float* prev = Xc;
+    int packed = 0;
     auto step = [&](const float* src, float* dst, double alpha, double beta, const float* Cprev,
-                    double gam) -> chfsi_status {
-      GemmDesc<float> g;
-      g.M = n;
-      g.N = b;
-      g.K = n;
+                    double gam, bool last) -> chfsi_status {
+      FilterProduct g;
       g.A = c->A32;
-      g.sak = 1;
-      g.sam = n;
+      g.n = n;
+      g.N = b;
       g.B = src;
-      g.sbk = 1;
-      g.sbn = n;
+      g.ldb = n;
       g.C = dst;
       g.ldc = n;
+      g.pack_next = !last;
       g.epi.alpha = float(alpha);
       g.epi.rowscale = c->dinv32;
       g.epi.beta = float(beta);
@@ -1228,19 +1222,19 @@ chfsi_status filter_chfsi(chfsi_ctx* c, const double* X, int64_t ldx, double* Yp
         g.epi.C2 = Cprev;
         g.epi.ldc2 = n;
       }
-      CK(prof_pair(c, &g.ev_begin, &g.ev_end));
-      CK(gemm<float>(g, c->stream, c->ws, filter_gemm_splits(), filter_gemm_cfg()));
+      const chfsi_status ps = dense_product(c, g, &packed);
+      if (ps != CHFSI_OK) return ps;
       fl += 2.0 * double(n) * double(n) * double(b);
       return CHFSI_OK;
     };
-    chfsi_status st = step(Xc, cur, f.sigma1 / f.e, -f.sigma1 * f.c / f.e, nullptr, 0.0);
+    chfsi_status st = step(Xc, cur, f.sigma1 / f.e, -f.sigma1 * f.c / f.e, nullptr, 0.0, p == 1);
     if (st != CHFSI_OK) return st;
     double sigma = f.sigma1;
     for (int k = 2; k <= p; ++k) {
       const double sigma2 = 1.0 / (gamma - sigma);
       const double a = 2.0 * sigma2 / f.e;
       float* dst = (prev == Xc) ? nxt : const_cast<float*>(prev);
-      st = step(cur, dst, a, -a * f.c, prev, -sigma * sigma2);
+      st = step(cur, dst, a, -a * f.c, prev, -sigma * sigma2, k == p);
       if (st != CHFSI_OK) return st;
       prev = cur;
       cur = dst;
@@ -2528,7 +2522,6 @@ chfsi_status chfsi::create_with_allocator(chfsi_ctx** out, const chfsi_operator*
     // blocks and the coefficient tables for 2b columns.
     const bool f64 = params->filter_prec == CHFSI_PREC_FP64;
     const size_t el = f64 ? sizeof(double) : sizeof(float);
-    const size_t lel = params->filter_prec == CHFSI_PREC_BF16 ? sizeof(uint16_t) : el;
     if (c->bloch) {
       if (!f64 && d_inv) c->dinv32 = ctx_alloc<float>(c, size_t(n) * sizeof(float), &st);
       if (!f64 && A->field_mode != 0) c->Vf = ctx_alloc<float>(c, size_t(n) * sizeof(float), &st);
@@ -2541,11 +2534,11 @@ chfsi_status chfsi::create_with_allocator(chfsi_ctx** out, const chfsi_operator*
         e = ctx_alloc<char>(c, size_t(2) * A->ny * A->nz * 2 * b * sel, &st);
       c->redge = ctx_alloc<double>(c, size_t(2) * A->ny * A->nz * 2 * b * sizeof(double), &st);
     } else {
-      c->Lc = ctx_alloc<char>(c, size_t(n) * 2 * n * lel, &st);
+      const size_t lb = f64 ? size_t(n) * 2 * n * el
+                            : filter_operator_bytes(n, 2, params->filter_prec == CHFSI_PREC_BF16 ? 1 : 3);
+      c->Lc = ctx_alloc<char>(c, lb, &st);
       c->dinv2 = ctx_alloc<char>(c, size_t(2) * n * el, &st);
-      size_t zt = size_t(2) * n * 2 * b * el;
-      if (params->filter_prec == CHFSI_PREC_BF16) zt += size_t(2) * n * 2 * b * sizeof(uint16_t);
-      c->Zt = ctx_alloc<char>(c, zt, &st);
+      if (f64) c->Zt = ctx_alloc<char>(c, size_t(2) * n * 2 * b * el, &st);
     }
     if (f64) {
       c->f64_a = ctx_alloc<double>(c, sp.f32blk, &st);
@@ -2606,7 +2599,7 @@ chfsi_status chfsi::create_with_allocator(chfsi_ctx** out, const chfsi_operator*
     c->ws_eig.bytes = sp.ws_eig;
     c->ws_eig.ptr = ctx_alloc<char>(c, sp.ws_eig, &st);
   } else if (params->filter_prec == CHFSI_PREC_FP32) {
-    if (dense) c->A32 = ctx_alloc<float>(c, size_t(n) * n * sizeof(float), &st);
+    if (dense) c->A32 = ctx_alloc<char>(c, filter_operator_bytes(n, 1, 3), &st);
     if (dense || d_inv) c->dinv32 = ctx_alloc<float>(c, size_t(n) * sizeof(float), &st);
     c->f32_a = ctx_alloc<float>(c, sp.f32blk, &st);
     c->f32_b = ctx_alloc<float>(c, sp.f32blk, &st);
@@ -2615,9 +2608,8 @@ chfsi_status chfsi::create_with_allocator(chfsi_ctx** out, const chfsi_operator*
     c->f64_a = ctx_alloc<double>(c, sp.f64blk, &st);
     c->f64_b = ctx_alloc<double>(c, sp.f64blk, &st);
   } else if (dense) {
-    c->A16 = ctx_alloc<uint16_t>(c, size_t(n) * n * sizeof(uint16_t), &st);
-    if (params->escalate) c->A32 = ctx_alloc<float>(c, size_t(n) * n * sizeof(float), &st);
-    c->bf_a = ctx_alloc<char>(c, size_t(n) * b * sizeof(uint16_t), &st);   // bf16(D^-1 R_Y)
+    c->A16 = ctx_alloc<char>(c, filter_operator_bytes(n, 1, 1), &st);
+    if (params->escalate) c->A32 = ctx_alloc<char>(c, filter_operator_bytes(n, 1, 3), &st);
     c->dinv32 = ctx_alloc<float>(c, size_t(n) * sizeof(float), &st);
     c->f32_a = ctx_alloc<float>(c, sp.f32blk, &st);
     c->f32_b = ctx_alloc<float>(c, sp.f32blk, &st);
@@ -2736,14 +2728,14 @@ chfsi_status chfsi::create_with_allocator(chfsi_ctx** out, const chfsi_operator*
     if (e == hipSuccess && params->filter_prec == CHFSI_PREC_FP64)
       e = dup_dinv<double>(d_inv, n, static_cast<double*>(c->dinv2), c->stream);
     if (e == hipSuccess && params->filter_prec == CHFSI_PREC_FP32)
-      e = herm_to_planar<float>(A->dense, A->ld, n, static_cast<float*>(c->Lc), c->stream);
+      e = pack_filter_operator(A->dense, A->ld, n, 2, 3, c->Lc, c->stream);
     if (e == hipSuccess && params->filter_prec == CHFSI_PREC_BF16)
-      e = herm_to_planar<uint16_t>(A->dense, A->ld, n, static_cast<uint16_t*>(c->Lc), c->stream);
+      e = pack_filter_operator(A->dense, A->ld, n, 2, 1, c->Lc, c->stream);
     if (e == hipSuccess && params->filter_prec != CHFSI_PREC_FP64)
       e = dup_dinv<float>(d_inv, n, static_cast<float*>(c->dinv2), c->stream);
   }
-  if (c->A32) e = convert_f64_f32(A->dense, A->ld, c->A32, n, n, n, c->stream);
-  if (e == hipSuccess && c->A16) e = convert_f64_bf16(A->dense, A->ld, c->A16, n, n, n, c->stream);
+  if (c->A32) e = pack_filter_operator(A->dense, A->ld, n, 1, 3, c->A32, c->stream);
+  if (e == hipSuccess && c->A16) e = pack_filter_operator(A->dense, A->ld, n, 1, 1, c->A16, c->stream);
   if (e == hipSuccess && c->dinv32) {
     if (d_inv)
       e = convert_f64_f32(d_inv, n, c->dinv32, n, n, 1, c->stream);

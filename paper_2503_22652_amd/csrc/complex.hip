@@ -464,17 +464,13 @@ hipError_t cluster_orthonormalize(double* E, int64_t lde, int64_t cd, int64_t nc
   return hipGetLastError();
 }
 
-template hipError_t herm_to_planar<float>(const double*, int64_t, int64_t, float*, hipStream_t);
 template hipError_t herm_to_planar<double>(const double*, int64_t, int64_t, double*, hipStream_t);
-template hipError_t herm_to_planar<uint16_t>(const double*, int64_t, int64_t, uint16_t*,
-                                             hipStream_t);
 template hipError_t dup_dinv<float>(const double*, int64_t, float*, hipStream_t);
 template hipError_t dup_dinv<double>(const double*, int64_t, double*, hipStream_t);
 template hipError_t cplx_init<float>(const double*, int64_t, int64_t, int64_t, double, float*,
                                      float*, float*, hipStream_t);
 template hipError_t cplx_init<double>(const double*, int64_t, int64_t, int64_t, double, double*,
                                       double*, double*, hipStream_t);
-template hipError_t cplx_rhs<float>(const float*, int64_t, int64_t, float*, hipStream_t);
 template hipError_t cplx_rhs<double>(const double*, int64_t, int64_t, double*, hipStream_t);
 template hipError_t cplx_reconstruct<float>(const float*, const double*, const double*, int64_t,
                                             const double*, double*, int64_t, int64_t, int64_t,

@@ -115,24 +115,36 @@ hipError_t gemm(const GemmDesc<T>& d, hipStream_t stream, const Workspace& ws,
 // Bytes of split-K scratch the heuristic may ask for at most for an M x N
 // output with reduction length K (per batch entry).
 size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K, size_t elem);
-// BF16 filter product: C = epilogue(A16 * bf16(kscale .* B)), A16 the
-// k-contiguous bfloat16 copy of the operator (ld lda16), B FP32 k-contiguous;
-// B16 (K x N bfloat16, ld K) receives the rounded right operand; FP32
-// accumulation and epilogue.  Split-K partials need at most
-// gemm_bf16_workspace_bytes(M, N) of ws.
-// Chained steps (M == K): b16_ready says B16 already holds bfloat16(kscale .*
-// B) and skips the rounding pass; with next16, the split-K reduction (when the
-// product takes it) also writes next16 (M x N, ld M) = bfloat16(next_scale .*
-// C) and sets *next_ready -- the next step's right operand, rounded from the
-// values just formed.  next16 may be B16: the reduction runs after the product.
-hipError_t gemm_bf16_filter(const GemmDesc<float>& d, const uint16_t* A16, int64_t lda16,
-                            uint16_t* B16, hipStream_t st, const Workspace& ws,
-                            int force_splits = 0, bool b16_ready = false,
-                            uint16_t* next16 = nullptr, const float* next_scale = nullptr,
-                            bool* next_ready = nullptr);
-size_t gemm_bf16_workspace_bytes(int64_t M, int64_t N);
-// split-K partial bytes the BF16 product will use for this shape (0: no split)
-size_t gemm_bf16_plan_bytes(int64_t M, int64_t N, int64_t K, int force_splits);
+// Dense filter step on bfloat16 matrix instructions (gemm_split.hip):
+//   C = epilogue(A (kscale .* B)),  A n x n (nseg = 1) or the planar [A_r | A_i]
+// n x 2n of a complex Hermitian operator with C, B planar n x N (nseg = 2).
+// planes = 3: A is FP32, the product of FP32 operands in three bfloat16 parts
+// each; planes = 1: A is bfloat16 and kscale .* B is rounded to it.
+// C may alias the epilogue's operands but not B.
+size_t filter_operator_bytes(int64_t n, int nseg, int planes);
+// the operator's packed copy, from FP64 dense symmetric A (nseg = 2: interleaved
+// complex Hermitian, lda in complex elements); out: filter_operator_bytes, 16-byte aligned
+hipError_t pack_filter_operator(const double* A, int64_t lda, int64_t n, int nseg, int planes,
+                                void* out, hipStream_t st);
+struct FilterProduct {
+  int planes = 3, nseg = 1;
+  const void* A = nullptr;         // packed
+  int64_t n = 0, N = 0;
+  const float* B = nullptr;
+  int64_t ldb = 0;
+  const float* kscale = nullptr;   // n
+  float* C = nullptr;
+  int64_t ldc = 0;
+  bool pack_next = false;          // the next step multiplies kscale .* C by the same A
+  Epilogue<float> epi;
+};
+// least bytes of ws
+size_t filter_product_bytes(int64_t n, int64_t N, int nseg, int planes);
+// *packed: 0, or what the step before (with pack_next, nothing having used ws
+// since) left there: the workspace then holds this step's right operand.
+// force_path (-1: by size) 1: split-K over workgroups and a reduction, 0: one launch.
+hipError_t filter_product(const FilterProduct& d, hipStream_t st, const Workspace& ws,
+                          int force_path, int force_splits, int* packed);
 
 // Which tile configuration/split the heuristic picks (for reports and tests).
 template <typename T>
@@ -144,7 +156,7 @@ void gemm_plan(int64_t M, int64_t N, int64_t K, int batch, int* config, int* spl
 // blocks are n x 2b (real parts, then imaginary parts), ld n.
 // ---------------------------------------------------------------------------
 // L (n x 2n, row m at L + m*2n) = [Re A(:,m), -Im A(:,m)]: the left operand of
-// the planar real product (F = float, double or uint16_t bfloat16)
+// the planar real product
 template <typename F>
 hipError_t herm_to_planar(const double* A, int64_t lda, int64_t n, F* L, hipStream_t st);
 // out[0..n) = out[n..2n) = dinv (1 when null)
@@ -282,8 +294,6 @@ hipError_t column_norms(const double* R, int64_t ldr, int64_t n, int64_t b, doub
 // FP64 -> FP32 copy of an n x m column-major matrix
 hipError_t convert_f64_f32(const double* in, int64_t ldi, float* out, int64_t ldo, int64_t n,
                            int64_t m, hipStream_t st);
-hipError_t convert_f64_bf16(const double* in, int64_t ldi, uint16_t* out, int64_t ldo, int64_t n,
-                            int64_t m, hipStream_t st);
 // copy an n x b block between leading dimensions
 hipError_t copy_block(const double* in, int64_t ldi, double* out, int64_t ldo, int64_t n,
                       int64_t b, hipStream_t st);
