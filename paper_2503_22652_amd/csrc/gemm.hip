@@ -29,6 +29,7 @@
 
 #include <algorithm>
 #include <cstdlib>
+#include <type_traits>
 
 namespace chfsi {
 
@@ -56,6 +57,7 @@ template <>
 struct Vec16<double> {
   static constexpr int W = 2;
   typedef double type __attribute__((ext_vector_type(2)));
+  typedef double utype __attribute__((ext_vector_type(2), aligned(8)));
 };
 
 struct KernelArgsCommon {
@@ -115,21 +117,28 @@ struct TileLoader {
   using vec_t = typename Vec16<T>::type;
   vec_t r[NV];
 
-  // Unchecked 16-byte loads: the whole tile lies inside the operand.
+  // 16-byte loads (8-byte aligned suffices) of a whole k slice.  CLAMP: the tile may
+  // reach past row rmax (rmax >= W); rows past it repeat rows inside, unused.
+  template <bool CLAMP>
   __device__ __forceinline__ void load_fast(const T* __restrict__ base, int64_t sr, int64_t r0,
-                                            int64_t k0, const T* __restrict__ kscale) {
+                                            int64_t rmax, int64_t k0) {
+    using ld_t = typename std::conditional<CLAMP, typename Vec16<T>::utype, vec_t>::type;
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
       const int v = threadIdx.x + i * 256;
       if (TOT % 256 != 0 && v >= TOT) break;
       if constexpr (KCONTIG) {
-        const int row = v / (BK / W);
         const int kk = (v % (BK / W)) * W;
-        r[i] = *reinterpret_cast<const vec_t*>(base + (r0 + row) * sr + k0 + kk);
+        int64_t row = r0 + v / (BK / W);
+        if (CLAMP) row = std::min(row, rmax - 1);
+        r[i] = *reinterpret_cast<const ld_t*>(base + row * sr + k0 + kk);
       } else {
         const int kk = v / (ROWS / W);
-        const int row = (v % (ROWS / W)) * W;
-        r[i] = *reinterpret_cast<const vec_t*>(base + r0 + row + (k0 + kk) * sr);
+        const int64_t row = r0 + (v % (ROWS / W)) * W;
+        const int64_t at = CLAMP ? std::min(row, rmax - W) : row;
+        r[i] = *reinterpret_cast<const ld_t*>(base + at + (k0 + kk) * sr);
+        // a vector moved back by one (an odd rmax): its second element is the first row
+        if (CLAMP && row == rmax - 1) r[i][0] = r[i][W - 1];
       }
     }
   }
@@ -183,14 +192,15 @@ struct TileLoader {
   }
 };
 
-// CHECK = false: every tile is interior and every k slice is full (M, N
-// multiples of the tile, K a multiple of BK, 16-byte aligned operands) -- the
-// host launches this variant only then; it carries no bounds checks at all.
-template <typename T, int BM, int BN, int BK, int MINW, bool AK, bool BKC, bool KS, bool CHECK>
+// WM x (4 / WM) waves.  CHECK = false: every tile is interior and every k slice is
+// full (M, N multiples of the tile, K a multiple of BK, 16-byte aligned operands)
+// -- the host launches this variant only then; it carries no bounds checks at all.
+template <typename T, int BM, int BN, int BK, int WM, int MINW, bool AK, bool BKC, bool KS,
+          bool CHECK>
 __global__ __launch_bounds__(256, MINW) void gemm_kernel(KernelArgs<T> args) {
   using MF = Mfma<T>;
   using acc_t = typename MF::acc_t;
-  constexpr int WM = 2, WN = 2;
+  constexpr int WN = 4 / WM;
   constexpr int PAD = 16 / sizeof(T);
   constexpr int LDK = BK + PAD;
   constexpr int KG = BK / 4;                 // k values per lane group per slice
@@ -223,9 +233,8 @@ __global__ __launch_bounds__(256, MINW) void gemm_kernel(KernelArgs<T> args) {
   const int64_t kbeg = int64_t(split) * c.kchunk;
   const int64_t kend = std::min<int64_t>(c.K, kbeg + c.kchunk);
   const int nk = kend > kbeg ? int((kend - kbeg + BK - 1) / BK) : 0;
-  // slices [0, nfull) of an interior tile need no bounds checks
-  const bool interior = !CHECK || (c.vecA && c.vecB && m0 + BM <= c.M && n0 + BN <= c.N);
-  const int nfull = !CHECK ? nk : (interior ? int((kend - kbeg) / BK) : 0);
+  // whole k slices load without bounds checks: rows past the edges repeat others
+  const int nfull = !CHECK ? nk : (c.M >= 2 && c.N >= 2 ? int((kend - kbeg) / BK) : 0);
 
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
@@ -252,8 +261,8 @@ __global__ __launch_bounds__(256, MINW) void gemm_kernel(KernelArgs<T> args) {
   auto load = [&](LA& la, LB& lb, T& kv, int s) __attribute__((always_inline)) {
     const int64_t k0 = kbeg + int64_t(s) * BK;
     if (!CHECK || s < nfull) {
-      la.load_fast(A, sA, m0, k0, nullptr);
-      lb.load_fast(B, sB, n0, k0, nullptr);
+      la.template load_fast<CHECK>(A, sA, m0, c.M, k0);
+      lb.template load_fast<CHECK>(B, sB, n0, c.N, k0);
     } else {
       la.load_checked(A, sA, m0, c.M, k0, kend, nullptr);
       lb.load_checked(B, sB, n0, c.N, k0, kend, nullptr);
@@ -393,9 +402,18 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(KernelArgs<T> args) 
     const int64_t bz = idx / MN;
     const int64_t e = idx - bz * MN;
     const int64_t m = e % c.M, n = e / c.M;
+    if (c.lower && n > (m | 63)) continue;   // tiles that were not formed
     const T* P = args.partial + bz * c.splits * MN + e;
     T s = T(0);
-    for (int q = 0; q < c.splits; ++q) s += P[q * MN];
+    int q = 0;
+    for (; q + 8 <= c.splits; q += 8) {   // eight loads in flight, added in split order
+      T x[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) x[u] = P[(q + u) * MN];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) s += x[u];
+    }
+    for (; q < c.splits; ++q) s += P[q * MN];
     Epilogue<T> ep = args.epi;
     if (ep.C1) ep.C1 += bz * c.bsC1;
     T* C = args.C + bz * c.bsC;
@@ -601,8 +619,10 @@ struct Cfg {
 };
 
 // Tile shapes.
-static const Cfg kCfgF64[] = {{128, 128, 16, 1}, {128, 64, 16, 2}, {64, 64, 16, 3}};
-static constexpr int kNumF64 = 3;
+static const Cfg kCfgF64[] = {{128, 128, 16, 1}, {128, 64, 16, 2}, {64, 64, 16, 3},
+                              {64, 16, 16, 4},   {64, 32, 16, 4}};
+static constexpr int kNumF64 = 5;
+static constexpr int kGeneral = 2;   // 64 x 64
 static constexpr int kNumCU = 256;
 
 // Tile/split choice.  Measured on MI355X (rocprofv3 + HIP events, the filter
@@ -612,13 +632,17 @@ static constexpr int kNumCU = 256;
 // force_config for other shapes.
 //
 // FP64 products with a long reduction (K >= 16 max(M, N), M, N >= 128: the
-// Gram matrices Y^T W of Rayleigh-Ritz) use 128 x 64 tiles and 8 k-splits.
-// The tile -> XCD remap then gives each XCD one k-range, whose panels every
-// tile on that XCD shares in its L2.  Measured on the 128^3 x 1200 grid
+// Gram matrices Y^T W of Rayleigh-Ritz).  Above 640 columns 128 x 64 tiles and 8
+// k-splits: the tile -> XCD remap then gives each XCD one k-range, whose panels
+// every tile on that XCD shares in its L2.  Measured on the 128^3 x 1200 grid
 // pencil (whole Rayleigh-Ritz, same process): 128x64 / 8 splits 375 ms,
 // 64x64 / 8 402 ms, 128x128 / 8 403 ms; 4 splits 456-593 ms; 16-64 splits
-// 610-990 ms (a k-range per XCD no longer holds).  Tuning knobs (read per
-// call): CHFSI_GEMM64_LONG_CFG (0 = 128x128, 1 = 128x64, 2 = 64x64) and
+// 610-990 ms (a k-range per XCD no longer holds).  Up to 640 columns that is too
+// few workgroups (72 on or below the diagonal at 300), and the panels of several
+// k-ranges fit an L2: 64 x 64 tiles, which waste less on the diagonal, and splits
+// up to 64.  Whole Rayleigh-Ritz, us, 128x64 / 8 and 64x64 / 64: 64^3 x 300 11245 and
+// 7329, 64^3 x 600 24926 and 18689, 40^3 x 200 4206 and 3193.  Tuning knobs (read
+// per call): CHFSI_GEMM64_LONG_CFG (0 = 128x128, 1 = 128x64, 2 = 64x64) and
 // CHFSI_GEMM64_LONG_SPLITS (power of two, at most 64).
 static int env_int(const char* name, int dflt) {
   const char* e = std::getenv(name);
@@ -627,17 +651,19 @@ static int env_int(const char* name, int dflt) {
 
 template <typename T>
 static void plan_impl(int64_t M, int64_t N, int64_t K, int batch, int* config, int* splits) {
-  const int ncfg = kNumF64;
   // the long-K rule also serves the complex Gram products (two batched
   // b x b blocks; knob CHFSI_GEMM64_LONG_BATCHED = 0 gives them the general plan)
   const bool long_batched = env_int("CHFSI_GEMM64_LONG_BATCHED", 1) > 0 && batch <= 2;
   if ((batch == 1 || long_batched) && M >= 128 && N >= 128 &&
       K >= 16 * std::max(M, N)) {
-    int lcfg = env_int("CHFSI_GEMM64_LONG_CFG", 1);
+    const bool wide = std::max(M, N) > 640;
+    int lcfg = env_int("CHFSI_GEMM64_LONG_CFG", wide ? 1 : kGeneral);
     if (lcfg < 0 || lcfg >= kNumF64) lcfg = 1;
-    const int lsplits = env_int("CHFSI_GEMM64_LONG_SPLITS", 8);
     const Cfg& w = kCfgF64[lcfg];
     const int64_t max_s = std::max<int64_t>(1, K / (8 * w.BK));
+    // narrow: about 2048 workgroups on and below the diagonal
+    const int64_t t = (std::max(M, N) + 63) / 64, low = t * (t + 1) / 2;
+    const int lsplits = env_int("CHFSI_GEMM64_LONG_SPLITS", wide ? 8 : int(2048 / low));
     int s = 1;
     while (s * 2 <= lsplits && s * 2 <= max_s && s < 64) s *= 2;
     *config = lcfg;
@@ -646,17 +672,33 @@ static void plan_impl(int64_t M, int64_t N, int64_t K, int batch, int* config, i
   }
   // FP64 products with a large output (M N >= 2^24, e.g. the grid rotation
   // X = Y Q): knob CHFSI_GEMM64_BIG_CFG (0 = 128x128, 1 = 128x64, 2 = 64x64)
-  int gcfg = ncfg - 1;
+  int gcfg = kGeneral;
   if (M * N >= (int64_t(1) << 24)) {
-    const int bc = env_int("CHFSI_GEMM64_BIG_CFG", ncfg - 1);
-    if (bc >= 0 && bc < ncfg) gcfg = bc;
+    const int bc = env_int("CHFSI_GEMM64_BIG_CFG", kGeneral);
+    if (bc >= 0 && bc < kNumF64) gcfg = bc;
   }
+  // (splits by the 64-wide tiling whatever the column tile: the partials' size and
+  // the order of summation do not depend on it)
   const Cfg& f = kCfgF64[gcfg];
   const int64_t tiles = ((M + f.BM - 1) / f.BM) * ((N + f.BN - 1) / f.BN) * batch;
   const int64_t target = int64_t(kNumCU) * 8;
   const int64_t max_s = std::max<int64_t>(1, K / (8 * f.BK));
   int s = 1;
   while (tiles * s < target && s * 2 <= max_s && s < 64) s *= 2;
+  // The column tile: the least work, padding included, at each one's rate relative
+  // to the 64-wide one's; where that leaves the chip half empty, the 32-wide one.
+  // Measured (plain filter of degree 16, us, tiles of 64 / 32 / 16): N = 3001, 16
+  // columns 508 / 361 / 347, 48 562 / 608 / 614, 77 965 / 820 / 900, 96 1007 / 850 /
+  // 1043, 128 1040 / 1074 / 1321; 6000 x 160 4268 / 4010 / 5470, 320 7010 / 7618 /
+  // 10212; 700 x 48 249 / 209 / 216.  (Tiles of 48 and 80 were no better at any of these.)
+  if (gcfg == kGeneral) {
+    auto cost = [N](int w, double rate) { return double((N + w - 1) / w * w) / rate; };
+    const double c64 = cost(64, 1.0), c32 = cost(32, 0.95), c16 = cost(16, 0.6);
+    if (c16 < std::min(c32, c64))
+      gcfg = 3;
+    else if (c32 < c64 || tiles * s < 2 * kNumCU)
+      gcfg = 4;
+  }
   *config = gcfg;
   *splits = s;
 }
@@ -671,7 +713,7 @@ size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K, size_t elem) {
   return size_t(64) * size_t(M) * size_t(N) * elem;
 }
 
-template <typename T, int BM, int BN, int BK, int MINW>
+template <typename T, int BM, int BN, int BK, int WM, int MINW>
 static hipError_t launch_cfg(const GemmDesc<T>& d, hipStream_t st, const Workspace& ws,
                              int splits) {
   KernelArgs<T> a;
@@ -741,23 +783,23 @@ static hipError_t launch_cfg(const GemmDesc<T>& d, hipStream_t st, const Workspa
   if (AK && BKC) {
     if (aligned) {
       if (KS)
-        gemm_kernel<T, BM, BN, BK, MINW, true, true, true, false><<<dim3(grid), dim3(256), 0, st>>>(a);
+        gemm_kernel<T, BM, BN, BK, WM, MINW, true, true, true, false><<<dim3(grid), dim3(256), 0, st>>>(a);
       else
-        gemm_kernel<T, BM, BN, BK, MINW, true, true, false, false><<<dim3(grid), dim3(256), 0, st>>>(a);
+        gemm_kernel<T, BM, BN, BK, WM, MINW, true, true, false, false><<<dim3(grid), dim3(256), 0, st>>>(a);
     } else {
       if (KS)
-        gemm_kernel<T, BM, BN, BK, MINW, true, true, true, true><<<dim3(grid), dim3(256), 0, st>>>(a);
+        gemm_kernel<T, BM, BN, BK, WM, MINW, true, true, true, true><<<dim3(grid), dim3(256), 0, st>>>(a);
       else
-        gemm_kernel<T, BM, BN, BK, MINW, true, true, false, true><<<dim3(grid), dim3(256), 0, st>>>(a);
+        gemm_kernel<T, BM, BN, BK, WM, MINW, true, true, false, true><<<dim3(grid), dim3(256), 0, st>>>(a);
     }
   } else if (KS) {
     return hipErrorInvalidValue;   // k-scaling is only used with k-contiguous operands
   } else if (AK && !BKC) {
-    gemm_kernel<T, BM, BN, BK, MINW, true, false, false, true><<<dim3(grid), dim3(256), 0, st>>>(a);
+    gemm_kernel<T, BM, BN, BK, WM, MINW, true, false, false, true><<<dim3(grid), dim3(256), 0, st>>>(a);
   } else if (!AK && BKC) {
-    gemm_kernel<T, BM, BN, BK, MINW, false, true, false, true><<<dim3(grid), dim3(256), 0, st>>>(a);
+    gemm_kernel<T, BM, BN, BK, WM, MINW, false, true, false, true><<<dim3(grid), dim3(256), 0, st>>>(a);
   } else {
-    gemm_kernel<T, BM, BN, BK, MINW, false, false, false, true><<<dim3(grid), dim3(256), 0, st>>>(a);
+    gemm_kernel<T, BM, BN, BK, WM, MINW, false, false, false, true><<<dim3(grid), dim3(256), 0, st>>>(a);
   }
   hipError_t err = hipGetLastError();
   if (err != hipSuccess) return err;
@@ -792,9 +834,11 @@ hipError_t gemm(const GemmDesc<T>& d, hipStream_t st, const Workspace& ws, int f
   hipError_t gerr = hipSuccess;
   if (force_config < 0 && force_splits <= 0 && gram_launch(d, st, ws, &gerr)) return gerr;
   switch (cfg) {
-    case 0: return launch_cfg<T, 128, 128, 16, 1>(d, st, ws, splits);
-    case 1: return launch_cfg<T, 128, 64, 16, 2>(d, st, ws, splits);
-    default: return launch_cfg<T, 64, 64, 16, 3>(d, st, ws, splits);
+    case 0: return launch_cfg<T, 128, 128, 16, 2, 1>(d, st, ws, splits);
+    case 1: return launch_cfg<T, 128, 64, 16, 2, 2>(d, st, ws, splits);
+    case 3: return launch_cfg<T, 64, 16, 16, 4, 3>(d, st, ws, splits);
+    case 4: return launch_cfg<T, 64, 32, 16, 2, 3>(d, st, ws, splits);
+    default: return launch_cfg<T, 64, 64, 16, 2, 3>(d, st, ws, splits);
   }
 }
 
