@@ -450,6 +450,7 @@ struct ZmArgs {
   int nx, ny, nz, ty, ntiles_y, b;
   int order;                 // workgroup -> tile order (see k_zmarch)
   int z0, nzs;               // output planes [z0, z0 + nzs)
+  int nzc, zc;               // ... in nzc ranges of zc planes, one workgroup each
   int use_w;                 // the stencil on w = V u is present (cw != 0)
   int64_t out_off;           // output row index = grid index - out_off
   F cu[4], cw[4], cm[4];     // class coefficients on u, on w = V u, and of M
@@ -526,14 +527,17 @@ void k_zmarch(ZmArgs<F> a) {
   // order 0: a column group's y-tiles are consecutive (they share halo rows);
   // order 1: the column groups of one y-tile are consecutive (they share the
   // potential's planes, which are 2 x the BF16 operand bytes)
-  int cg, ytile;
+  int cg, ytile, zr;
   if (a.order == 0) {
-    cg = t / a.ntiles_y;
-    ytile = t - cg * a.ntiles_y;
+    const int q = t / a.ntiles_y;
+    ytile = t - q * a.ntiles_y;
+    cg = q / a.nzc;
+    zr = q - cg * a.nzc;
   } else {
-    const int ncg = nb / a.ntiles_y;
-    ytile = t / ncg;
-    cg = t - ytile * ncg;
+    const int ncg = nb / (a.ntiles_y * a.nzc), q = t / ncg;
+    cg = t - q * ncg;
+    ytile = q / a.nzc;
+    zr = q - ytile * a.nzc;
   }
   const int y0 = ytile * TY, tyn = min(TY, ny - y0);
   // group g (256 threads) owns columns col0 .. col0 + ncol - 1
@@ -744,7 +748,7 @@ void k_zmarch(ZmArgs<F> a) {
   F accK[CP][PT], accKn[CP][PT], accM[CP][PT], accMn[CP][PT];
   // potential at this thread's points of the next output plane (from staging)
   FV vcur;
-  const int zb = a.z0, ze = a.z0 + a.nzs;
+  const int zb = a.z0 + zr * a.zc, ze = min(zb + a.zc, a.z0 + a.nzs);
   auto wz = [&](int z) { return z < 0 ? z + nz : (z >= nz ? z - nz : z); };
 
   // The next plane and the next output's epilogue operands are loaded one
@@ -978,8 +982,8 @@ bool zm_setup(const chfsi_operator& op, int PT, int CP, double alpha, double bet
   a->nx = op.nx;
   a->ny = op.ny;
   a->nz = op.nz;
-  a->ty = std::min(256 / tpr, op.ny);
-  a->ntiles_y = (op.ny + a->ty - 1) / a->ty;
+  a->ntiles_y = (op.ny + std::min(256 / tpr, op.ny) - 1) / std::min(256 / tpr, op.ny);
+  a->ty = (op.ny + a->ntiles_y - 1) / a->ntiles_y;   // tiles as equal as they can be
   a->z0 = 0;
   a->nzs = op.nz;
   a->out_off = 0;
@@ -1008,11 +1012,36 @@ int zm_order(bool hasv) {
   return hasv ? 1 : 0;
 }
 
+// Ranges of z planes to cut nzs planes into, one workgroup each, for `tiles` (column
+// group, y tile) pairs: a range of zc planes stages and combines zc + 2.  A CU works
+// on about five workgroups at a time; alone, a workgroup takes about twice as long
+// a plane as when five share the CU (1.1 against 0.55 us of CU time a plane, 60 x 52
+// x 44 x 33 and 128^3 x 160), so few tiles gain from a cut and many lose by it.
+// Measured, us a filter pass, whole and cut: 60 x 52 x 44 x 33 FP32 (132 tiles, degree
+// 20) 1037 and 462, 64^3 x 96 BF16 Bloch (384 tiles, degree 30) 4363 and 2929.
+inline int zm_ranges(int64_t tiles, int nzs) {
+  int best = 1;
+  double tbest = 0.0;
+  for (int c = 1; c <= std::max(1, nzs / 2); ++c) {
+    const int zc = (nzs + c - 1) / c;
+    const int64_t w = tiles * ((nzs + zc - 1) / zc);
+    const double t = (zc + 2) * std::max(2.0 * double((w + 1279) / 1280), double(w) / 256.0);
+    if (c == 1 || t < 0.95 * tbest) {
+      best = c;
+      tbest = t;
+    }
+  }
+  return best;
+}
+
 template <typename S, typename F, int PT, int CP, int NG, int KIND>
 hipError_t zm_launch_ng(const ZmArgs<F>& a, bool hasv, hipStream_t st) {
   const int per = CP * NG;
-  const int64_t grid = int64_t((a.b + per - 1) / per) * a.ntiles_y;
+  const int64_t tiles = int64_t((a.b + per - 1) / per) * a.ntiles_y;
   ZmArgs<F> ar = a;
+  ar.zc = (a.nzs + zm_ranges(tiles, a.nzs) - 1) / zm_ranges(tiles, a.nzs);
+  ar.nzc = (a.nzs + ar.zc - 1) / ar.zc;
+  const int64_t grid = tiles * ar.nzc;
   ar.order = zm_order(hasv);
   const size_t lds = zm_lds_bytes(a.nx, a.ty, per, hasv, sizeof(F));
   if (lds > 65536) return hipErrorInvalidValue;
@@ -1059,10 +1088,10 @@ hipError_t zm_launch(const ZmArgs<F>& a, bool hasv, hipStream_t st) {
   const ZmShape sh = zm_shape(sizeof(F) == 4);
   if constexpr (sizeof(F) == 8) {
     // FP64: at most 2 groups (4 would cap the kernel at 128 VGPRs and spill)
-    if (sh.ng == 1) return zm_launch_ng<S, F, PT, 1, 1, KIND>(a, hasv, st);
+    if (PT == 1 || sh.ng == 1) return zm_launch_ng<S, F, PT, 1, 1, KIND>(a, hasv, st);
     return zm_launch_ng<S, F, PT, 1, 2, KIND>(a, hasv, st);
-  } else if constexpr (PT == 2) {
-    return zm_launch_ng<S, F, 2, 1, 1, KIND>(a, hasv, st);
+  } else if constexpr (PT <= 2) {
+    return zm_launch_ng<S, F, PT, 1, 1, KIND>(a, hasv, st);
   } else {
     if (sh.cp == 2) {
       if (sh.ng == 1) return zm_launch_ng<S, F, PT, 2, 1, KIND>(a, hasv, st);
@@ -1075,10 +1104,20 @@ hipError_t zm_launch(const ZmArgs<F>& a, bool hasv, hipStream_t st) {
   }
 }
 
-// points per thread of the FP32/BF16 filter steps (tuning knob CHFSI_STENCIL_PT)
-int zm_pt_lowp() {
+// Points per thread: 4 (FP32 arithmetic; tuning knob CHFSI_STENCIL_PT = 2 for 2), or as
+// many as divide the row: 2, or 1.  Measured, us a pass of degree 20, the scalar kernel
+// (which such rows took) and this one: 61 x 52 x 44 x 33 FP32 4597 and 555, 62 x 52 x 44 x
+// 33 BF16 4687 and 515, 95 x 90 x 97 x 60 BF16 14877 and 4082 (96 points: 3355).
+int zm_pt(int nx, bool lowp) {
   static const int v = zm_env("CHFSI_STENCIL_PT");
-  return v == 2 ? 2 : 4;
+  if (lowp && v != 2 && nx % 4 == 0 && nx >= 8) return 4;
+  return nx % 2 == 0 && nx >= 4 ? 2 : 1;
+}
+template <typename S, typename F, int KIND>
+hipError_t zm_launch_pt(const ZmArgs<F>& a, int pt, bool hasv, hipStream_t st) {
+  if constexpr (sizeof(F) == 4)
+    if (pt == 4) return zm_launch<S, F, 4, KIND>(a, hasv, st);
+  return pt == 2 ? zm_launch<S, F, 2, KIND>(a, hasv, st) : zm_launch<S, F, 1, KIND>(a, hasv, st);
 }
 
 // columns sharing one workgroup's staged planes (for the LDS-size check)
@@ -1130,15 +1169,16 @@ double stencil_flops(const chfsi_operator& op) {
 hipError_t stencil_apply_f64(const chfsi_operator& op, const double* X, int64_t ldx, double* Y,
                              int64_t ldy, int64_t b, hipStream_t st) {
   ZmArgs<double> z;
-  if (zm_setup(op, 2, zm_per_wg(false), 1.0, 0.0, &z) && zm_aligned(X, ldx, 16, 2) && zm_aligned(Y, ldy, 16, 2) &&
-      zm_aligned(op.field, 0, 16, 2)) {
+  const int pt = zm_pt(op.nx, false);
+  if (zm_setup(op, pt, zm_per_wg(false), 1.0, 0.0, &z) && zm_aligned(X, ldx, 8 * pt, pt) && zm_aligned(Y, ldy, 8 * pt, pt) &&
+      zm_aligned(op.field, 0, 8 * pt, pt)) {
     z.b = int(b);
     z.V = op.field;
     z.src = X;
     z.ld_src = ldx;
     z.out = Y;
     z.ld_out = ldy;
-    return zm_launch<double, double, 2, ZM_APPLY>(z, op.field_mode != 0, st);
+    return zm_launch_pt<double, double, ZM_APPLY>(z, pt, op.field_mode != 0, st);
   }
   SepArgs<double> a;
   if (sep_setup(op, &a)) {
@@ -1159,9 +1199,10 @@ hipError_t stencil_rchfsi_step_f64(const chfsi_operator& op, const double* dinv,
                                    hipStream_t st, const BlochStep* bloch) {
   if (bloch && (b % 2 != 0 || bloch->ld_corr % 4 != 0)) return hipErrorInvalidValue;
   ZmArgs<double> z;
-  if (!dinv && RX && Yf && zm_setup(op, 2, zm_per_wg(false), s.alpha, s.beta, &z) &&
-      zm_aligned(RY, op.n, 16, 2) && zm_aligned(RX, op.n, 16, 2) && zm_aligned(Yf, ldf, 16, 2) &&
-      zm_aligned(op.field, 0, 16, 2)) {
+  const int pt = zm_pt(op.nx, false);
+  if (!dinv && RX && Yf && zm_setup(op, pt, zm_per_wg(false), s.alpha, s.beta, &z) &&
+      zm_aligned(RY, op.n, 8 * pt, pt) && zm_aligned(RX, op.n, 8 * pt, pt) && zm_aligned(Yf, ldf, 8 * pt, pt) &&
+      zm_aligned(op.field, 0, 8 * pt, pt)) {
     z.b = int(b);
     z.V = op.field;
     z.src = RY;
@@ -1184,9 +1225,9 @@ hipError_t stencil_rchfsi_step_f64(const chfsi_operator& op, const double* dinv,
       z.corr = corr;
       z.ld_corr = bloch->ld_corr;
       z.edge_out = bloch->edge_out;
-      return zm_launch<double, double, 2, ZM_BSTEP>(z, op.field_mode != 0, st);
+      return zm_launch_pt<double, double, ZM_BSTEP>(z, pt, op.field_mode != 0, st);
     }
-    return zm_launch<double, double, 2, ZM_STEP>(z, op.field_mode != 0, st);
+    return zm_launch_pt<double, double, ZM_STEP>(z, pt, op.field_mode != 0, st);
   }
   SepArgs<double> a;
   if (sep_setup(op, &a)) {
@@ -1219,7 +1260,7 @@ hipError_t stencil_rchfsi_step_f32(const chfsi_operator& op, const float* Vf, co
                                    const BlochStep* bloch) {
   if (bloch && (b % 2 != 0 || bloch->ld_corr % 4 != 0)) return hipErrorInvalidValue;
   ZmArgs<float> z;
-  const int pt = zm_pt_lowp();
+  const int pt = zm_pt(op.nx, true);
   const size_t vb = size_t(pt) * sizeof(float);
   if (!dinv && RX && Yf && (op.field_mode == 0 || Vf) &&
       zm_setup(op, pt, zm_per_wg(true), s.alpha, s.beta, &z) && zm_aligned(RY, op.n, vb, pt) &&
@@ -1246,11 +1287,9 @@ hipError_t stencil_rchfsi_step_f32(const chfsi_operator& op, const float* Vf, co
       z.corr = corr;
       z.ld_corr = bloch->ld_corr;
       z.edge_out = bloch->edge_out;
-      return pt == 2 ? zm_launch<float, float, 2, ZM_BSTEP>(z, op.field_mode != 0, st)
-                     : zm_launch<float, float, 4, ZM_BSTEP>(z, op.field_mode != 0, st);
+      return zm_launch_pt<float, float, ZM_BSTEP>(z, pt, op.field_mode != 0, st);
     }
-    return pt == 2 ? zm_launch<float, float, 2, ZM_STEP>(z, op.field_mode != 0, st)
-                   : zm_launch<float, float, 4, ZM_STEP>(z, op.field_mode != 0, st);
+    return zm_launch_pt<float, float, ZM_STEP>(z, pt, op.field_mode != 0, st);
   }
   SepArgs<float> a;
   if (sep_setup(op, &a)) {
@@ -1286,7 +1325,7 @@ hipError_t stencil_rchfsi_step_bf16(const chfsi_operator& op, const float* Vf, c
   if (bloch && (b % 2 != 0 || bloch->ld_corr % 4 != 0)) return hipErrorInvalidValue;
   const uint16_t* RY16 = static_cast<const uint16_t*>(RY);
   ZmArgs<float> z;
-  const int pt = zm_pt_lowp();
+  const int pt = zm_pt(op.nx, true);
   const size_t vb = size_t(pt) * 2, vf = size_t(pt) * sizeof(float);
   if (!dinv && RX && Yf && (op.field_mode == 0 || Vf) &&
       zm_setup(op, pt, zm_per_wg(true), s.alpha, s.beta, &z) && zm_aligned(RY, op.n, vb, pt) &&
@@ -1313,11 +1352,9 @@ hipError_t stencil_rchfsi_step_bf16(const chfsi_operator& op, const float* Vf, c
       z.corr = corr;
       z.ld_corr = bloch->ld_corr;
       z.edge_out = bloch->edge_out;
-      return pt == 2 ? zm_launch<uint16_t, float, 2, ZM_BSTEP>(z, op.field_mode != 0, st)
-                     : zm_launch<uint16_t, float, 4, ZM_BSTEP>(z, op.field_mode != 0, st);
+      return zm_launch_pt<uint16_t, float, ZM_BSTEP>(z, pt, op.field_mode != 0, st);
     }
-    return pt == 2 ? zm_launch<uint16_t, float, 2, ZM_STEP>(z, op.field_mode != 0, st)
-                   : zm_launch<uint16_t, float, 4, ZM_STEP>(z, op.field_mode != 0, st);
+    return zm_launch_pt<uint16_t, float, ZM_STEP>(z, pt, op.field_mode != 0, st);
   }
   SepArgs<float> a;
   if (sep_setup(op, &a)) {
@@ -1351,9 +1388,10 @@ hipError_t stencil_chfsi_step_f64(const chfsi_operator& op, const double* dinv, 
                                   int64_t lds, const double* prev, int64_t ldp, double* dst,
                                   StencilStep s, int64_t b, hipStream_t st) {
   ZmArgs<double> z;
-  if (!dinv && zm_setup(op, 2, zm_per_wg(false), s.alpha, s.beta, &z) && zm_aligned(src, lds, 16, 2) &&
-      zm_aligned(prev, ldp, 16, 2) && zm_aligned(dst, op.n, 16, 2) &&
-      zm_aligned(op.field, 0, 16, 2)) {
+  const int pt = zm_pt(op.nx, false);
+  if (!dinv && zm_setup(op, pt, zm_per_wg(false), s.alpha, s.beta, &z) && zm_aligned(src, lds, 8 * pt, pt) &&
+      zm_aligned(prev, ldp, 8 * pt, pt) && zm_aligned(dst, op.n, 8 * pt, pt) &&
+      zm_aligned(op.field, 0, 8 * pt, pt)) {
     z.b = int(b);
     z.V = op.field;
     z.src = src;
@@ -1363,7 +1401,7 @@ hipError_t stencil_chfsi_step_f64(const chfsi_operator& op, const double* dinv, 
     z.e1 = prev;
     z.ld_e1 = ldp;
     z.gamma = s.gamma;
-    return zm_launch<double, double, 2, ZM_CSTEP>(z, op.field_mode != 0, st);
+    return zm_launch_pt<double, double, ZM_CSTEP>(z, pt, op.field_mode != 0, st);
   }
   SepArgs<double> a;
   if (sep_setup(op, &a)) {
@@ -1407,8 +1445,9 @@ hipError_t stencil_apply_slab_f64(const chfsi_operator& op, const double* X, int
                                   hipStream_t st) {
   if (z0 < 0 || nzs < 1 || z0 + nzs > op.nz) return hipErrorInvalidValue;
   ZmArgs<double> z;
-  if (zm_setup(op, 2, zm_per_wg(false), 1.0, 0.0, &z) && zm_aligned(X, ldx, 16, 2) && zm_aligned(Yslab, ldy, 16, 2) &&
-      zm_aligned(op.field, 0, 16, 2)) {
+  const int pt = zm_pt(op.nx, false);
+  if (zm_setup(op, pt, zm_per_wg(false), 1.0, 0.0, &z) && zm_aligned(X, ldx, 8 * pt, pt) && zm_aligned(Yslab, ldy, 8 * pt, pt) &&
+      zm_aligned(op.field, 0, 8 * pt, pt)) {
     z.b = int(b);
     z.z0 = z0;
     z.nzs = nzs;
@@ -1418,7 +1457,7 @@ hipError_t stencil_apply_slab_f64(const chfsi_operator& op, const double* X, int
     z.ld_src = ldx;
     z.out = Yslab;
     z.ld_out = ldy;
-    return zm_launch<double, double, 2, ZM_APPLY>(z, op.field_mode != 0, st);
+    return zm_launch_pt<double, double, ZM_APPLY>(z, pt, op.field_mode != 0, st);
   }
   SepArgs<double> a;
   if (!sep_setup(op, &a)) return hipErrorInvalidValue;
@@ -1437,9 +1476,10 @@ hipError_t stencil_residual_f64(const chfsi_operator& A, const chfsi_operator* B
                                 int64_t ldx, const double* lam, double* R, int64_t ldr, int64_t b,
                                 hipStream_t st) {
   ZmArgs<double> z;
+  const int pt = zm_pt(A.nx, false);
   double cb[4] = {1.0, 0.0, 0.0, 0.0};
-  if ((!B || class_symmetric(B->coef, cb)) && zm_setup(A, 2, zm_per_wg(false), 1.0, 0.0, &z) &&
-      zm_aligned(X, ldx, 16, 2) && zm_aligned(R, ldr, 16, 2) && zm_aligned(A.field, 0, 16, 2)) {
+  if ((!B || class_symmetric(B->coef, cb)) && zm_setup(A, pt, zm_per_wg(false), 1.0, 0.0, &z) &&
+      zm_aligned(X, ldx, 8 * pt, pt) && zm_aligned(R, ldr, 8 * pt, pt) && zm_aligned(A.field, 0, 8 * pt, pt)) {
     for (int k = 0; k < 4; ++k) z.cb[k] = cb[k];
     z.b = int(b);
     z.V = A.field;
@@ -1448,7 +1488,7 @@ hipError_t stencil_residual_f64(const chfsi_operator& A, const chfsi_operator* B
     z.out = R;
     z.ld_out = ldr;
     z.colcoef = lam;
-    return zm_launch<double, double, 2, ZM_RESID>(z, A.field_mode != 0, st);
+    return zm_launch_pt<double, double, ZM_RESID>(z, pt, A.field_mode != 0, st);
   }
   SepArgs<double> a;
   if (!sep_setup(A, &a)) return hipErrorInvalidValue;
