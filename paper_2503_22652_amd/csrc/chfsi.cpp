@@ -34,10 +34,20 @@ namespace {
 // as a breakdown: the smallest eigenvalue is then below 1e-14 times the largest
 // (which is at least 1), so the SVQB reading would drop a direction.
 constexpr double kGramPivotTol = 1e-14;
-hipError_t potrf_traced(double* A, int64_t lda, int64_t b, int* info, hipStream_t st,
+// L over A and, in one launch with it where L fits one workgroup, L^{-1} over Li
+// (which a failed pivot leaves as it was); cholqr_inverse forms it otherwise.
+hipError_t potrf_traced(double* A, int64_t b, double* Li, int* info, hipStream_t st,
                         const Workspace& ws, double* tri) {
   TraceRange tr("chfsi cholqr factor");
-  return potrf_lower(A, lda, b, info, st, ws, tri, kGramPivotTol);
+  if (potrf_inverse_fits(b)) return potrf_inverse(A, b, b, info, Li, b, st, kGramPivotTol);
+  return potrf_lower(A, b, b, info, st, ws, tri, kGramPivotTol);
+}
+
+hipError_t cholqr_inverse(double* A, int64_t b, double* Li, hipStream_t st, const Workspace& ws,
+                          double* tri) {
+  if (potrf_inverse_fits(b)) return hipSuccess;
+  if (hipError_t e = set_identity(Li, b, b, st); e != hipSuccess) return e;
+  return trsm_lower_left(A, b, Li, b, b, b, st, ws, tri);
 }
 
 // the eigensolver under a roctx range; pinned (two ints of pinned host memory)
@@ -1473,7 +1483,7 @@ chfsi_status rayleigh_ritz(chfsi_ctx* c, const double* Y, int64_t ldy, double* X
   // column scaling s = diag(Gb)^{-1/2}; Cholesky of the scaled Gram matrix
   CK(scale_gram(c->Gb, b, b, c->Gs, b, c->svec, c->dflags + 1, st));
   CK(copy_block(c->Gs, b, c->Linv, b, b, b, st));      // kept for the SVQB fallback
-  CK(potrf_traced(c->Gs, b, b, c->dflags, st, c->ws, c->tri));
+  CK(potrf_traced(c->Gs, b, c->Linv, c->dflags, st, c->ws, c->tri));
   CK(hipMemcpyAsync(c->h_flags, c->dflags, 4 * sizeof(int), hipMemcpyDeviceToHost, st));
   CK(hipStreamSynchronize(st));
   if (c->h_flags[1] != 0) {
@@ -1489,8 +1499,7 @@ chfsi_status rayleigh_ritz(chfsi_ctx* c, const double* Y, int64_t ldy, double* X
     return rayleigh_ritz_svqb(c, Y, ldy, BY, ldby, X, ldx, R, ldr, ritz, resnorm);
   }
   // Linv = L^{-1}
-  CK(set_identity(c->Linv, b, b, st));
-  CK(trsm_lower_left(c->Gs, b, c->Linv, b, b, b, st, c->ws, c->tri, true));
+  CK(cholqr_inverse(c->Gs, b, c->Linv, st, c->ws, c->tri));
   // Hp = Linv (s Ga s) Linv^T
   CK(scale_sym(c->Ga, b, b, c->svec, c->Hp, b, st));
   {
@@ -1896,7 +1905,7 @@ chfsi_status rayleigh_ritz_complex(chfsi_ctx* c, const double* Y, int64_t ldy, d
   // CholQR of the scaled embedded Gram matrix, projected matrix, Jacobi
   CK(scale_gram(c->Gb, m, m, c->Gs, m, c->svec, c->dflags + 1, st));
   CK(copy_block(c->Gs, m, c->Linv, m, m, m, st));      // kept for the SVQB fallback
-  CK(potrf_traced(c->Gs, m, m, c->dflags, st, c->ws, c->tri));
+  CK(potrf_traced(c->Gs, m, c->Linv, c->dflags, st, c->ws, c->tri));
   CK(hipMemcpyAsync(c->h_flags, c->dflags, 4 * sizeof(int), hipMemcpyDeviceToHost, st));
   CK(hipStreamSynchronize(st));
   if (c->h_flags[1] != 0) {
@@ -1911,8 +1920,7 @@ chfsi_status rayleigh_ritz_complex(chfsi_ctx* c, const double* Y, int64_t ldy, d
     }
     return rayleigh_ritz_complex_svqb(c, Y, ldy, X, ldx, R, ldr, ritz, resnorm, tail);
   }
-  CK(set_identity(c->Linv, m, m, st));
-  CK(trsm_lower_left(c->Gs, m, c->Linv, m, m, m, st, c->ws, c->tri, true));
+  CK(cholqr_inverse(c->Gs, m, c->Linv, st, c->ws, c->tri));
   CK(scale_sym(c->Ga, m, m, c->svec, c->Hp, m, st));
   {
     GemmDesc<double> g;   // Tmp = Linv Hp
@@ -2065,7 +2073,7 @@ chfsi_status rayleigh_ritz_slabs(chfsi_ctx* c, double* X, int64_t ldx, double* R
   if ((s = slab_grams(c, X, ldx)) != CHFSI_OK) return s;
   CK(scale_gram(c->Gb, b, b, c->Gs, b, c->svec, c->dflags + 1, st));
   CK(copy_block(c->Gs, b, c->Linv, b, b, b, st));
-  CK(potrf_traced(c->Gs, b, b, c->dflags, st, c->ws, c->tri));
+  CK(potrf_traced(c->Gs, b, c->Linv, c->dflags, st, c->ws, c->tri));
   CK(hipMemcpyAsync(c->h_flags, c->dflags, 4 * sizeof(int), hipMemcpyDeviceToHost, st));
   CK(hipStreamSynchronize(st));
   if (c->h_flags[1] != 0) {
@@ -2074,8 +2082,7 @@ chfsi_status rayleigh_ritz_slabs(chfsi_ctx* c, double* X, int64_t ldx, double* R
   }
   int sweeps = 0;
   if (c->h_flags[0] == 0) {
-    CK(set_identity(c->Linv, b, b, st));
-    CK(trsm_lower_left(c->Gs, b, c->Linv, b, b, b, st, c->ws, c->tri, true));
+    CK(cholqr_inverse(c->Gs, b, c->Linv, st, c->ws, c->tri));
     CK(scale_sym(c->Ga, b, b, c->svec, c->Hp, b, st));
     GemmDesc<double> g;
     g.M = b;
@@ -2380,7 +2387,7 @@ chfsi_status form_exact_operator(chfsi_ctx* c, const chfsi_operator* A, const ch
       return CHFSI_ERR_NOT_SPD;
     }
     CK(set_identity(Li, n, n, st));
-    CK(trsm_lower_left(L, n, Li, n, n, n, st, c->ws, tri, true));
+    CK(trsm_lower_left(L, n, Li, n, n, n, st, c->ws, tri));
     {
       GemmDesc<double> g;   // B^{-1} = L^{-T} L^{-1}, into L
       g.M = n;

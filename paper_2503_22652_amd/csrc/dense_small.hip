@@ -32,61 +32,29 @@ namespace chfsi {
 namespace {
 
 constexpr int NB = 64;          // Cholesky / TRSM block
+constexpr int kCholTiles = 8;   // 16-row tiles of the largest one-workgroup Cholesky (LDS)
 constexpr int JB = 16;          // Jacobi column block
 constexpr int JP = 2 * JB;      // Jacobi pair subproblem size
 constexpr int LDJ = JP + 1;     // padded LDS leading dimension
 
-// ---------------------------------------------------------------------------
-// Cholesky of the diagonal block (jb <= 64) in LDS; right-looking, one barrier
-// per column: step k subtracts a_ik a_jk / d_k (d_k = a_kk at step k) from the
-// trailing lower triangle, the columns are scaled by 1/sqrt(d_k) at the end.
-// Threads form a 16 x 16 grid over the trailing triangle (no index division).
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_potrf_diag(double* A, int64_t lda, int jb, int* info,
-                                                    int j0, double piv_tol) {
-  __shared__ double a[NB * (NB + 1)];
-  constexpr int L = NB + 1;
-  if (*info != 0) return;
-  for (int idx = threadIdx.x; idx < jb * jb; idx += 256) {
-    const int i = idx % jb, j = idx / jb;
-    a[i + j * L] = A[i + j * lda];
-  }
-  __syncthreads();
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  for (int k = 0; k < jb; ++k) {
-    const double d = a[k + k * L];
-    if (!(d > piv_tol) || !isfinite(d)) {  // the same decision in every thread
-      if (threadIdx.x == 0) atomicCAS(info, 0, j0 + k + 1);
-      return;
-    }
-    const double inv = 1.0 / d;
-    for (int j = k + 1 + ty; j < jb; j += 16) {
-      const double ljk = a[j + k * L] * inv;
-      for (int i = j + tx; i < jb; i += 16) a[i + j * L] -= a[i + k * L] * ljk;
-    }
-    __syncthreads();
-  }
-  for (int idx = threadIdx.x; idx < jb * jb; idx += 256) {
-    const int i = idx % jb, j = idx / jb;
-    const double dj = sqrt(a[j + j * L]);
-    A[i + j * lda] = i > j ? a[i + j * L] / dj : (i == j ? dj : 0.0);
-  }
-}
-
-// Cholesky of the diagonal block (jb <= NB) and the inverse of its factor in
-// one wave: lane i holds row i in registers (the block padded to NB x NB with
-// the identity).  Step k: the pivot d = a_kk is read from lane k, g = 1/sqrt(d)
-// comes from the hardware estimate and two Newton steps, lane i forms
-// l_ik = a_ik g (l_kk = d g) and puts it in LDS (two alternating buffers), and
-// every lane subtracts l_ik l_jk from its row (the l_jk are LDS broadcasts).
-// Then lane c forms column c of L^{-1} by forward substitution with the
-// pivots' g, reading the rows of L from LDS in 16-byte pairs; the sum of each
-// step runs in four partial sums (j mod 4), which shortens the chain of
-// dependent FP64 operations fourfold.  Writes L (upper part of the block
-// zeroed) and L^{-1} (NB x NB, ld NB, identity-padded) to Li.  The steps are
-// expanded from templates, so every register index is a constant.  Measured
-// at b = 320 (five blocks per factorisation): see the kernel table.
-constexpr int LDR = NB + 2;     // row stride of L in LDS (16-byte aligned rows)
+// Cholesky factor L and its inverse of one matrix of up to 16 NT rows, in one
+// workgroup of eight waves, the matrix in LDS in 16 x 16 tiles (padded with the
+// identity).  Per tile column: wave 0 factors and inverts the 16 x 16 diagonal tile
+// in registers (lane i holds row i; the pivots and the entries of L travel by
+// readlane; 1/sqrt(d) from the hardware estimate and two Newton steps), all waves
+// form the tiles below with the inverse and update the trailing tiles on
+// v_mfma_f64_16x16x4.  Then each wave forms the inverse's tiles of one tile column
+// from the top down, Linv_ij = -Linv_ii sum_k L_ik Linv_kj (the sum's accumulator has
+// the right operand's layout).  L fills the lower triangle of the LDS matrix, L^{-1}
+// transposed the strictly upper one, its diagonal an array of its own.
+// A chain of dependent FP64 operations bounds it (16 pivots a tile).  Straight-line
+// code over all 64 columns in one wave, 53 us for 64 rows, spent its time fetching
+// instructions; this takes 33 us for 64 rows and 42 us
+// for 80 with the whole inverse (two such blocks and the products between them: 190).
+//   A (lda): jb x jb in, L out (upper part zeroed).  Li (li_n x li_n, ldi): L^{-1},
+// identity-padded past jb.  A pivot that is not above piv_tol (or not finite) sets
+// *info to j0 + its 1-based column, and nothing is written.
+typedef double chol_f64x4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ double readlane_f64(double v, int lane) {
   const unsigned long long u = __double_as_longlong(v);
@@ -104,107 +72,155 @@ __device__ __forceinline__ double rsqrt_newton(double x) {
   return fma(0.5 * y, e, y);
 }
 
-template <int K>
-__device__ __forceinline__ bool chol_step(double (&r)[NB], double (*col)[NB], double* invd,
-                                          double piv_tol) {
-  const int i = threadIdx.x;
-  const double d = readlane_f64(r[K], K);
-  if (!(d > piv_tol) || !isfinite(d)) return false;   // the same decision in every lane
-  const double g = rsqrt_newton(d);
-  const double l = i == K ? d * g : r[K] * g;
-  r[K] = l;
-  col[K & 1][i] = l;
-  if (i == 0) invd[K] = g;
-  __syncthreads();
-#pragma unroll
-  for (int j = K + 1; j < NB; ++j) r[j] = fma(-l, col[K & 1][j], r[j]);
-  return true;
-}
-
-template <int K>
-__device__ __forceinline__ void trtri_step(double (&x)[NB], const double* lt, const double* invd) {
-  double s[4] = {(int(threadIdx.x) == K) ? 1.0 : 0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-  for (int j = 0; j < K; ++j) s[j & 3] = fma(-lt[K * LDR + j], x[j], s[j & 3]);
-  x[K] = ((s[0] + s[1]) + (s[2] + s[3])) * invd[K];
-}
-
-template <int... Ks>
-__device__ __forceinline__ int chol_all(std::integer_sequence<int, Ks...>, double (&r)[NB],
-                                        double (*col)[NB], double* invd, double piv_tol) {
-  int failed = -1;
-  // left to right; a failed pivot stops the remaining steps
-  ((failed < 0 && !chol_step<Ks>(r, col, invd, piv_tol) ? (failed = Ks) : 0), ...);
-  return failed;
-}
-
-template <int... Ks>
-__device__ __forceinline__ void trtri_all(std::integer_sequence<int, Ks...>, double (&x)[NB],
-                                          const double* lt, const double* invd) {
-  (trtri_step<Ks>(x, lt, invd), ...);
-}
-
-__global__ __launch_bounds__(64) void k_potrf_trtri_diag(double* A, int64_t lda, int jb,
-                                                         int* info, int j0, double* Li,
-                                                         double piv_tol) {
-  __shared__ __attribute__((aligned(16))) double col[2][NB];
-  __shared__ __attribute__((aligned(16))) double lt[NB * LDR];
-  __shared__ double invd[NB];
+template <int NT>
+__global__ __launch_bounds__(512) void k_chol_inv(double* A, int64_t lda, int jb, int* info, int j0,
+                                                  double* Li, int64_t ldi, int li_n,
+                                                  double piv_tol) {
+  constexpr int LD = 16 * NT + 1;
+  __shared__ double S[16 * NT * LD];
+  __shared__ double invd[16 * NT];
+  __shared__ int bad;
   if (*info != 0) return;
-  const int i = threadIdx.x;
-  double r[NB];
-#pragma unroll
-  for (int j = 0; j < NB; ++j)
-    r[j] = (i < jb && j < jb) ? A[i + j * lda] : (i == j ? 1.0 : 0.0);
-  const int failed = chol_all(std::make_integer_sequence<int, NB>{}, r, col, invd, piv_tol);
-  if (failed >= 0) {
-    if (i == 0) atomicCAS(info, 0, j0 + failed + 1);
-    return;
-  }
-  // L (lower, zero above): row i to LDS (row-major) and to the block
-#pragma unroll
-  for (int j = 0; j < NB; ++j) lt[i * LDR + j] = j <= i ? r[j] : 0.0;
-  if (i < jb) {
-#pragma unroll
-    for (int j = 0; j < NB; ++j)
-      if (j < jb) A[i + j * lda] = j <= i ? r[j] : 0.0;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int l16 = lane & 15, g = lane >> 4;
+  const int nt = (std::max(jb, li_n) + 15) / 16, np = 16 * nt;
+  if (tid == 0) bad = 0;
+  for (int idx = tid; idx < np * np; idx += 512) {
+    const int i = idx % np, j = idx / np;
+    S[i + j * LD] = (i < jb && j < jb) ? (i >= j ? A[i + j * lda] : 0.0) : (i == j ? 1.0 : 0.0);
   }
   __syncthreads();
-  // column i of L^{-1}: x_k = (delta_ki - sum_{j<k} l_kj x_j) / l_kk
-  double x[NB];
-  trtri_all(std::make_integer_sequence<int, NB>{}, x, lt, invd);
+  // entry (i, k) of the inverse of diagonal tile t
+  auto inv_diag = [&](int t, int i, int k) __attribute__((always_inline)) {
+    const double up = S[(16 * t + k) + (16 * t + i) * LD];
+    return k < i ? up : (k == i ? invd[16 * t + i] : 0.0);
+  };
+  for (int p = 0; p < nt; ++p) {
+    const int c0 = 16 * p;
+    if (wave == 0) {
+      double r[16], x[16], gd[16];
 #pragma unroll
-  for (int k = 0; k < NB; ++k) Li[k + i * NB] = x[k];
-}
-
-// Inverse of one lower-triangular diagonal block (jb <= NB) of L: one wave,
-// lane c forms column c of L^{-1} by forward substitution in registers
-// (entries above the diagonal are zero).  Block blockIdx.x starts at row and
-// column j0 + blockIdx.x * NB.
-__global__ __launch_bounds__(64) void k_trtri_diag(const double* L, int64_t ldl, int64_t b,
-                                                   int64_t j0, double* Li, const int* info) {
-  __shared__ double l[NB * (NB + 1)];
-  constexpr int LD = NB + 1;
-  if (info && *info != 0) return;
-  const int64_t o = j0 + int64_t(blockIdx.x) * NB;
-  const int jb = int(b - o < NB ? b - o : NB);
-  for (int idx = threadIdx.x; idx < NB * NB; idx += 64) {
-    const int i = idx % NB, j = idx / NB;
-    l[i + j * LD] = (i < jb && j < jb) ? L[(o + i) + (o + j) * ldl] : (i == j ? 1.0 : 0.0);
+      for (int j = 0; j < 16; ++j) r[j] = S[(c0 + l16) + (c0 + j) * LD];
+      int failed = -1;
+#pragma unroll
+      for (int k = 0; k < 16; ++k) {
+        const double d = readlane_f64(r[k], k);
+        if (failed < 0 && (!(d > piv_tol) || !isfinite(d))) failed = k;
+        gd[k] = rsqrt_newton(d);
+        const double l = l16 == k ? d * gd[k] : r[k] * gd[k];
+        r[k] = l;
+#pragma unroll
+        for (int j = k + 1; j < 16; ++j) r[j] = fma(-l, readlane_f64(l, j), r[j]);
+      }
+      if (failed >= 0) {
+        if (lane == 0) {
+          bad = 1;
+          atomicCAS(info, 0, j0 + c0 + failed + 1);
+        }
+      } else {
+        // column l16 of the tile's inverse
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+          double s0 = l16 == k ? 1.0 : 0.0, s1 = 0.0;
+#pragma unroll
+          for (int j = 0; j < k; ++j) {
+            const double lkj = readlane_f64(r[j], k);
+            if (j & 1)
+              s1 = fma(-lkj, x[j], s1);
+            else
+              s0 = fma(-lkj, x[j], s0);
+          }
+          x[k] = (s0 + s1) * gd[k];
+        }
+        if (lane < 16) {
+#pragma unroll
+          for (int j = 0; j < 16; ++j) {
+            if (j <= l16) S[(c0 + l16) + (c0 + j) * LD] = r[j];
+            // Linv(j, l16), j > l16, transposed
+            if (j > l16) S[(c0 + l16) + (c0 + j) * LD] = x[j];
+          }
+#pragma unroll
+          for (int j = 0; j < 16; ++j)
+            if (j == l16) invd[c0 + j] = x[j];
+        }
+      }
+    }
+    __syncthreads();
+    if (bad) return;
+    // the tiles below: L_tp = A_tp Linv_pp^T
+    for (int t = p + 1 + wave; t < nt; t += 8) {
+      chol_f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+      double a[4], b[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        a[q] = S[(16 * t + l16) + (c0 + 4 * q + g) * LD];
+        b[q] = inv_diag(p, l16, 4 * q + g);
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[q], b[q], acc, 0, 0, 0);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) S[(16 * t + g + 4 * q) + (c0 + l16) * LD] = acc[q];
+    }
+    __syncthreads();
+    // the trailing tiles: A_ts -= L_tp L_sp^T
+    const int m = nt - 1 - p, ntile = m * (m + 1) / 2;
+    for (int u = wave; u < ntile; u += 8) {
+      int ti = 0, rem = u;
+      while (rem > ti) {
+        rem -= ti + 1;
+        ++ti;
+      }
+      const int rt = 16 * (p + 1 + ti), ct = 16 * (p + 1 + rem);
+      chol_f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+      double a[4], b[4], o[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        a[q] = S[(rt + l16) + (c0 + 4 * q + g) * LD];
+        b[q] = S[(ct + l16) + (c0 + 4 * q + g) * LD];
+        o[q] = S[(rt + g + 4 * q) + (ct + l16) * LD];
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[q], b[q], acc, 0, 0, 0);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) S[(rt + g + 4 * q) + (ct + l16) * LD] = o[q] - acc[q];
+    }
+    __syncthreads();
+  }
+  // the inverse's tiles below the diagonal, tile column j by wave j (its own
+  // results only: no barrier)
+  for (int j = wave; j < nt; j += 8) {
+    for (int i = j + 1; i < nt; ++i) {
+      chol_f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+      for (int k = j; k < i; ++k) {
+        double a[4], b[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int kk = 4 * q + g;
+          a[q] = S[(16 * i + l16) + (16 * k + kk) * LD];
+          b[q] = k == j ? inv_diag(j, kk, l16) : S[(16 * j + l16) + (16 * k + kk) * LD];
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[q], b[q], acc, 0, 0, 0);
+      }
+      chol_f64x4 o = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        o = __builtin_amdgcn_mfma_f64_16x16x4f64(inv_diag(i, l16, 4 * q + g), -acc[q], o, 0, 0, 0);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) S[(16 * j + l16) + (16 * i + g + 4 * q) * LD] = o[q];
+      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    }
   }
   __syncthreads();
-  const int c = threadIdx.x;
-  double x[NB];
-#pragma unroll
-  for (int k = 0; k < NB; ++k) {
-    double s = (k == c) ? 1.0 : 0.0;
-#pragma unroll
-    for (int j = 0; j < k; ++j) s -= l[k + j * LD] * x[j];
-    x[k] = s / l[k + k * LD];
+  for (int idx = tid; idx < jb * jb; idx += 512) {
+    const int i = idx % jb, j = idx / jb;
+    A[i + j * lda] = i >= j ? S[i + j * LD] : 0.0;
   }
-  double* out = Li + int64_t(blockIdx.x) * NB * NB;
-#pragma unroll
-  for (int k = 0; k < NB; ++k) out[k + c * NB] = x[k];
+  for (int idx = tid; idx < li_n * li_n; idx += 512) {
+    const int i = idx % li_n, j = idx / li_n;
+    Li[i + j * ldi] = i > j ? S[j + i * LD] : (i == j ? invd[i] : 0.0);
+  }
 }
 
 __global__ __launch_bounds__(256) void k_zero_upper(double* A, int64_t lda, int64_t b) {
@@ -1022,16 +1038,21 @@ size_t tri_workspace_bytes(int64_t b, int64_t nrhs) {
   return size_t(nblk * NB * NB + NB * std::max(b, nrhs)) * sizeof(double);
 }
 
+bool potrf_inverse_fits(int64_t b) { return b <= 16 * kCholTiles; }
+
+hipError_t potrf_inverse(double* A, int64_t lda, int64_t b, int* info, double* Linv, int64_t ldi,
+                         hipStream_t st, double piv_tol) {
+  if (!potrf_inverse_fits(b)) return hipErrorInvalidValue;
+  if (b <= NB)
+    k_chol_inv<NB / 16><<<1, 512, 0, st>>>(A, lda, int(b), info, 0, Linv, ldi, int(b), piv_tol);
+  else
+    k_chol_inv<kCholTiles><<<1, 512, 0, st>>>(A, lda, int(b), info, 0, Linv, ldi, int(b), piv_tol);
+  return hipGetLastError();
+}
+
 // Blocked right-looking Cholesky.  Per diagonal block: factor it in LDS,
 // invert it (kept in tri for trsm_lower_left), form the panel below as a GEMM
 // with the inverse, then update the trailing matrix with a GEMM.
-// one-wave Cholesky-and-inverse of the diagonal blocks (knob CHFSI_POTRF_FUSED=0:
-// the 256-thread Cholesky and a separate inverse)
-static bool potrf_fused() {
-  const char* e = std::getenv("CHFSI_POTRF_FUSED");
-  return !(e && std::atoi(e) == 0);
-}
-
 hipError_t potrf_lower(double* A, int64_t lda, int64_t b, int* info, hipStream_t st,
                        const Workspace& ws, double* tri, double piv_tol) {
   hipError_t e = hipSuccess;
@@ -1040,16 +1061,9 @@ hipError_t potrf_lower(double* A, int64_t lda, int64_t b, int* info, hipStream_t
   for (int64_t j0 = 0; j0 < b; j0 += NB) {
     const int jb = int(std::min<int64_t>(NB, b - j0));
     double* Li = tri + (j0 / NB) * NB * NB;
-    if (potrf_fused()) {
-      k_potrf_trtri_diag<<<1, 64, 0, st>>>(A + j0 + j0 * lda, lda, jb, info, int(j0), Li,
+    k_chol_inv<NB / 16><<<1, 512, 0, st>>>(A + j0 + j0 * lda, lda, jb, info, int(j0), Li, NB, NB,
                                            piv_tol);
-      if ((e = hipGetLastError()) != hipSuccess) return e;
-    } else {
-      k_potrf_diag<<<1, 256, 0, st>>>(A + j0 + j0 * lda, lda, jb, info, int(j0), piv_tol);
-      if ((e = hipGetLastError()) != hipSuccess) return e;
-      k_trtri_diag<<<1, 64, 0, st>>>(A, lda, b, j0, Li, info);
-      if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
+    if ((e = hipGetLastError()) != hipSuccess) return e;
     const int64_t rows = b - j0 - jb;
     if (rows <= 0) break;
     {   // tmp (rows x jb) = A21 L11^{-T}; A21 <- tmp
@@ -1093,18 +1107,12 @@ hipError_t potrf_lower(double* A, int64_t lda, int64_t b, int* info, hipStream_t
 }
 
 // X <- L^{-1} X by block forward substitution with the diagonal blocks'
-// inverses (computed here unless inverses_ready, i.e. left in tri by
-// potrf_lower for the same L).
+// inverses that potrf_lower left in tri for the same L.
 hipError_t trsm_lower_left(const double* L, int64_t ldl, double* X, int64_t ldx, int64_t b,
-                           int64_t nrhs, hipStream_t st, const Workspace& ws, double* tri,
-                           bool inverses_ready) {
+                           int64_t nrhs, hipStream_t st, const Workspace& ws, double* tri) {
   hipError_t e = hipSuccess;
   const int64_t nblk = (b + NB - 1) / NB;
   double* tmp = tri + nblk * NB * NB;
-  if (!inverses_ready) {
-    k_trtri_diag<<<dim3(unsigned(nblk)), 64, 0, st>>>(L, ldl, b, 0, tri, nullptr);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-  }
   for (int64_t j0 = 0; j0 < b; j0 += NB) {
     const int jb = int(std::min<int64_t>(NB, b - j0));
     {   // tmp (jb x nrhs) = L_jj^{-1} X_j; X_j <- tmp

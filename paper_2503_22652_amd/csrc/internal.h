@@ -333,11 +333,15 @@ size_t tri_workspace_bytes(int64_t b, int64_t nrhs);
 // (1-based) that is not above piv_tol (or not finite), or 0
 hipError_t potrf_lower(double* A, int64_t lda, int64_t b, int* info, hipStream_t st,
                        const Workspace& ws, double* tri, double piv_tol = 0.0);
-// X <- L^{-1} X (L lower b x b, X b x nrhs); inverses_ready: tri holds the
-// diagonal blocks' inverses of this L (left by potrf_lower)
+// potrf_lower and the factor's whole inverse (b x b, ldi, upper part zeroed) in one
+// launch, for b that fit one workgroup's LDS; on a failed pivot Linv is left as it was
+bool potrf_inverse_fits(int64_t b);
+hipError_t potrf_inverse(double* A, int64_t lda, int64_t b, int* info, double* Linv, int64_t ldi,
+                         hipStream_t st, double piv_tol = 0.0);
+// X <- L^{-1} X (L lower b x b, X b x nrhs); tri holds the diagonal blocks'
+// inverses of this L (left by potrf_lower)
 hipError_t trsm_lower_left(const double* L, int64_t ldl, double* X, int64_t ldx, int64_t b,
-                           int64_t nrhs, hipStream_t st, const Workspace& ws, double* tri,
-                           bool inverses_ready);
+                           int64_t nrhs, hipStream_t st, const Workspace& ws, double* tri);
 // Symmetric eigensolver (parallel block Jacobi).  A (b x b) is destroyed.
 // w: ascending eigenvalues (device, b); V: eigenvectors (device, b x b, ldv).
 // scratch from ws; sweeps reported through *sweeps_out (host) if non-null;
