@@ -49,8 +49,9 @@ constexpr int LDJ = JP + 1;     // padded LDS leading dimension
 // transposed the strictly upper one, its diagonal an array of its own.
 // A chain of dependent FP64 operations bounds it (16 pivots a tile).  Straight-line
 // code over all 64 columns in one wave, 53 us for 64 rows, spent its time fetching
-// instructions; this takes 33 us for 64 rows and 42 us
-// for 80 with the whole inverse (two such blocks and the products between them: 190).
+// instructions; this takes 33 us for 64 rows, and
+// 42 us for 80 with the whole inverse (before, two such blocks and a dozen products
+// and copies).
 //   A (lda): jb x jb in, L out (upper part zeroed).  Li (li_n x li_n, ldi): L^{-1},
 // identity-padded past jb.  A pivot that is not above piv_tol (or not finite) sets
 // *info to j0 + its 1-based column, and nothing is written.
@@ -63,13 +64,12 @@ __device__ __forceinline__ double readlane_f64(double v, int lane) {
   return __longlong_as_double((static_cast<unsigned long long>(hi) << 32) | lo);
 }
 
-// 1/sqrt(x) for normal x > 0: the hardware estimate and two Newton steps
-__device__ __forceinline__ double rsqrt_newton(double x) {
-  double y = __builtin_amdgcn_rsq(x);
-  double e = fma(-(x * y), y, 1.0);
-  y = fma(0.5 * y, e, y);
-  e = fma(-(x * y), y, 1.0);
-  return fma(0.5 * y, e, y);
+// 1/sqrt(x) for normal x > 0: the hardware estimate (within 2^-24) and one step of
+// third order, y (1 + e/2 + 3 e^2 / 8) with e = 1 - x y^2
+__device__ __forceinline__ double rsqrt_f64(double x) {
+  const double y = __builtin_amdgcn_rsq(x);
+  const double e = fma(-(x * y), y, 1.0);
+  return fma(y * e, fma(0.375, e, 0.5), y);
 }
 
 template <int NT>
@@ -106,7 +106,7 @@ __global__ __launch_bounds__(512) void k_chol_inv(double* A, int64_t lda, int jb
       for (int k = 0; k < 16; ++k) {
         const double d = readlane_f64(r[k], k);
         if (failed < 0 && (!(d > piv_tol) || !isfinite(d))) failed = k;
-        gd[k] = rsqrt_newton(d);
+        gd[k] = rsqrt_f64(d);
         const double l = l16 == k ? d * gd[k] : r[k] * gd[k];
         r[k] = l;
 #pragma unroll
@@ -267,28 +267,26 @@ __device__ __forceinline__ int pair_index(int l, int I, int J) {
 // slot order) is kept.  The rotation of pair k acts on (first, second) =
 // (slot k, slot JP-1-k): J = [[c, s], [-s, c]], a <- J^T a J.
 //  * wave 0, lane k < JP/2: the rotation of pair k in the NEXT round.  The
-//    three entries it needs after this round are formed from this round's
-//    buffer and rotations with the same arithmetic (rot_block, same operand
-//    order) as the update waves, so they are bit-identical to what those
-//    waves store.
-//  * waves 2..4 (k1 >= k2 of 16 x 16 pair blocks, 136 threads): this round's
+//    three entries it needs after this round are formed with the same arithmetic
+//    (rot_entry, rot_block, same operand order) as in the update waves, so they are
+//    bit-identical to what those waves store: the diagonal, kept in registers and moved
+//    on between lanes, and one entry of this round's buffer.
+//  * waves 1..3 (k1 >= k2 of 16 x 16 pair blocks, 136 threads): this round's
 //    two-sided update of one 2 x 2 block each.
-//  * wave 1, lane i < JP: row i of the accumulated rotation U in registers,
-//    by index (the round loop is unrolled, so the indices of each round's
-//    pairs are constants).
+//  * waves 4..7, 16 lanes a row: two rows of the accumulated rotation U, by slot, in
+//    registers; the slots move on between lanes.
+// Wave 0's chain (barrier, LDS, one entry, two square roots) bounds a round.  Unrolled
+// loops (25 KB of code for U, 60 KB for wave 0), with all of it in LDS, took 15.8 us a
+// launch on average at 80 columns and 18.8 at 300; so it takes 12.2 and 14.9.
 // ---------------------------------------------------------------------------
 constexpr int kHalf = JP / 2;       // rotations per round
 constexpr int kRounds = JP - 1;     // rounds per sweep
-constexpr int kPairThreads = 5 * 64;
+constexpr int kPairThreads = 8 * 64;
 
 // lower-triangle LDS offset of symmetric entry (i, j) (slot coordinates)
 __device__ __forceinline__ int sym_idx(int i, int j) { return i >= j ? i + j * LDJ : j + i * LDJ; }
-// slot of an index after one round, and before it
+// slot of an index after one round
 __device__ __forceinline__ int slot_next(int s) { return s == 0 ? 0 : (s == 1 ? JP - 1 : s - 1); }
-__device__ __forceinline__ int slot_prev(int s) { return s == 0 ? 0 : (s == JP - 1 ? 1 : s + 1); }
-// pair of slot s, and whether s is the pair's first slot
-__device__ __forceinline__ int slot_pair(int s) { return s < kHalf ? s : JP - 1 - s; }
-
 // out = J1^T X J2 for the 2 x 2 block X (rows first/second of pair 1,
 // columns first/second of pair 2); explicit fma so that every caller rounds
 // alike
@@ -303,13 +301,12 @@ __device__ __forceinline__ void rot_block(double x11, double x12, double x21, do
   *o22 = fma(s2, y21, c2 * y22);
 }
 
-// 1/sqrt(x) for normal x > 0: the hardware estimate and two Newton steps
-__device__ __forceinline__ double rsqrt_nr(double x) {
-  double y = __builtin_amdgcn_rsq(x);
-  double e = fma(-(x * y), y, 1.0);
-  y = fma(0.5 * y, e, y);
-  e = fma(-(x * y), y, 1.0);
-  return fma(0.5 * y, e, y);
+// one output of rot_block with the same operations: (p1, q1) = (c1, -s1) for a first
+// row, (s1, c1) for a second one, (p2, q2) likewise for the column
+__device__ __forceinline__ double rot_entry(double x11, double x12, double x21, double x22,
+                                            double p1, double q1, double p2, double q2) {
+  const double y1 = fma(p1, x11, q1 * x21), y2 = fma(p1, x12, q1 * x22);
+  return fma(p2, y1, q2 * y2);
 }
 
 // rotation (c, s) with J^T [[app, apq], [apq, aqq]] J diagonal (apq != 0):
@@ -318,24 +315,25 @@ __device__ __forceinline__ double rsqrt_nr(double x) {
 // c = g / sqrt(g^2 + e^2), s = sign(d) e / sqrt(g^2 + e^2), two square roots
 // and no division.  Outside the range where d^2 + e^2 is a normal number the
 // textbook form with divisions is used.
-__device__ __forceinline__ void jacobi_cs(double app, double aqq, double apq, double* c,
-                                          double* s) {
+// No rotation (c = 1, s = 0) at |apq| <= thresh.
+__device__ __forceinline__ void jacobi_cs(double app, double aqq, double apq, double thresh,
+                                          double* c, double* s) {
   const double d = aqq - app, e = 2.0 * apq;
-  const double h2 = fma(d, d, e * e);
-  if (h2 > 1e-300 && h2 < 1e300) {
-    const double h = h2 * rsqrt_nr(h2);
-    const double g = fabs(d) + h;
-    const double r = rsqrt_nr(fma(g, g, e * e));
-    *c = g * r;
-    *s = (d < 0.0 ? -e : e) * r;
-    return;
+  const double e2 = e * e, h2 = fma(e, e, d * d);
+  const double g = fma(h2, rsqrt_f64(h2), fabs(d));
+  const double r = rsqrt_f64(fma(g, g, e2));
+  const bool rot = fabs(apq) > thresh, normal = h2 > 1e-300 && h2 < 1e300;
+  double cc = g * r, ss = (d < 0.0 ? -e : e) * r;
+  if (__builtin_expect(rot && !normal, 0)) {
+    const double theta = d / e;
+    const double t = fabs(theta) > 1e150
+                         ? 0.5 / theta
+                         : copysign(1.0, theta) / (fabs(theta) + sqrt(theta * theta + 1.0));
+    cc = 1.0 / sqrt(t * t + 1.0);
+    ss = t * cc;
   }
-  const double theta = d / e;
-  const double t = fabs(theta) > 1e150
-                       ? 0.5 / theta
-                       : copysign(1.0, theta) / (fabs(theta) + sqrt(theta * theta + 1.0));
-  *c = 1.0 / sqrt(t * t + 1.0);
-  *s = t * (*c);
+  *c = rot ? cc : 1.0;
+  *s = rot ? ss : 0.0;
 }
 
 // LDS of one pair subproblem: the slot-ordered lower triangle (ping-pong
@@ -346,6 +344,27 @@ struct PairSmem {
   double wmax[kPairThreads / 64];
   int nrot_total;
 };
+
+// value of lane + 1 (shl) or lane - 1 (shr) within each 16 lanes, `edge` in the last
+// (first) of them
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double edge, double v) {
+  const unsigned long long o = __double_as_longlong(edge), u = __double_as_longlong(v);
+  const unsigned lo = __builtin_amdgcn_update_dpp(int(o), int(u), CTRL, 0xf, 0xf, false);
+  const unsigned hi =
+      __builtin_amdgcn_update_dpp(int(o >> 32), int(u >> 32), CTRL, 0xf, 0xf, false);
+  return __longlong_as_double((static_cast<unsigned long long>(hi) << 32) | lo);
+}
+__device__ __forceinline__ double lane_shl(double edge, double v) { return dpp_f64<0x101>(edge, v); }
+__device__ __forceinline__ double lane_shr(double edge, double v) { return dpp_f64<0x111>(edge, v); }
+
+// lane k of 16 holds the values in slots k (v1) and JP - 1 - k (v2): move them on by
+// one round
+__device__ __forceinline__ void slot_shift(int k, double* v1, double* v2) {
+  const double up = lane_shl(*v2, *v1);    // from slot k + 1
+  *v2 = lane_shr(up, *v2);                 // from slot JP - k; pair 0's from slot 1
+  *v1 = k == 0 ? *v1 : up;
+}
 
 // One inner sweep of the pair subproblem held in S.buf[0] (lower triangle,
 // local order = slot order of round 0); `mx` is this thread's largest
@@ -373,62 +392,53 @@ __device__ __forceinline__ void pair_solve_core(PairSmem& S, double mx, const do
     if (tid == 0) *skip_out = 1;
     return;
   }
-  if (wave == 0 && lane < kHalf) {
-    const int f = lane, s = JP - 1 - lane;
-    const double apq = buf[0][sym_idx(s, f)];
-    double c = 1.0, sn = 0.0;
-    if (fabs(apq) > thresh) jacobi_cs(buf[0][sym_idx(f, f)], buf[0][sym_idx(s, s)], apq, &c, &sn);
-    cs[0][lane] = make_double2(c, sn);
+  // wave 0, every 16 lanes alike: lane k holds its pair's three entries (diagonal d1,
+  // d2, off-diagonal od) and rotation
+  const int k = lane & (kHalf - 1);
+  double d1 = 0.0, d2 = 0.0, od = 0.0, c = 1.0, sn = 0.0;
+  if (wave == 0) {
+    const int s = JP - 1 - k;
+    d1 = buf[0][sym_idx(k, k)];
+    d2 = buf[0][sym_idx(s, s)];
+    od = buf[0][sym_idx(s, k)];
+    jacobi_cs(d1, d2, od, thresh, &c, &sn);
+    if (lane < kHalf) cs[0][lane] = make_double2(c, sn);
   }
   __syncthreads();
   if (wave == 0) {
-    // next-round pair `lane` = this round's slots x (first) and y (second)
-    const int k = lane < kHalf ? lane : 0;
-    const int x = slot_prev(k), y = slot_prev(JP - 1 - k);
-    const int kx = slot_pair(x), ky = slot_pair(y);
-    // diagonal blocks of kx and ky: first/second slots and which output
-    const int fx = kx, sx = JP - 1 - kx, fy = ky, sy = JP - 1 - ky;
-    const int ax_ff = sym_idx(fx, fx), ax_sf = sym_idx(sx, fx), ax_ss = sym_idx(sx, sx);
-    const int ay_ff = sym_idx(fy, fy), ay_sf = sym_idx(sy, fy), ay_ss = sym_idx(sy, sy);
-    const bool x_first = x == fx, y_first = y == fy;
-    // off-diagonal (y, x): block (K1, K2) = rows of the pair with the larger index
-    const bool xrow = kx > ky;
-    const int K1 = xrow ? kx : ky, K2 = xrow ? ky : kx;
-    const int f1 = K1, s1 = JP - 1 - K1, f2 = K2, s2 = JP - 1 - K2;
-    const int b11 = sym_idx(f1, f2), b12 = sym_idx(f1, s2), b21 = sym_idx(s1, f2),
-              b22 = sym_idx(s1, s2);
-    const int rowv = xrow ? x : y, colv = xrow ? y : x;
-    const int osel = (rowv == f1 ? 0 : 2) + (colv == f2 ? 0 : 1);
-    int count = 0;
-    for (int r = 0; r < kRounds; ++r) {
+    // next-round pair k joins this round's slots h and l, of the pairs k + 1 (15: its
+    // own) and k - 1 (0: its own); entry (h, l) is one of that block pair's four
+    const int kh = k < kHalf - 1 ? k + 1 : k, kl = k > 0 ? k - 1 : 0;
+    const int fh = kh, sh = JP - 1 - kh, fl = kl, sl = JP - 1 - kl;
+    const int b11 = sym_idx(fh, fl), b12 = sym_idx(fh, sl), b21 = sym_idx(sh, fl),
+              b22 = sym_idx(sh, sl);
+    int count = sn != 0.0;
+    // the chain that bounds the kernel: first on its SIMD
+    __builtin_amdgcn_s_setprio(3);
+#pragma unroll 1
+    for (int r = 0; r + 1 < kRounds; ++r) {
       const double* a = buf[r & 1];
-      const double2* t = cs[r & 1];
-      if (lane < kHalf) {
-        const unsigned long long m = __ballot(t[lane].y != 0.0);
-        if (r + 1 < kRounds) {
-          const double2 tx = t[kx], ty = t[ky], t1 = t[K1], t2 = t[K2];
-          double o11, o12, o21, o22;
-          const double xsf = a[ax_sf];
-          rot_block(a[ax_ff], xsf, xsf, a[ax_ss], tx.x, tx.y, tx.x, tx.y, &o11, &o12, &o21, &o22);
-          const double app = x_first ? o11 : o22;
-          const double ysf = a[ay_sf];
-          rot_block(a[ay_ff], ysf, ysf, a[ay_ss], ty.x, ty.y, ty.x, ty.y, &o11, &o12, &o21, &o22);
-          const double aqq = y_first ? o11 : o22;
-          rot_block(a[b11], a[b12], a[b21], a[b22], t1.x, t1.y, t2.x, t2.y, &o11, &o12, &o21,
-                    &o22);
-          const double apq = osel == 0 ? o11 : (osel == 1 ? o12 : (osel == 2 ? o21 : o22));
-          double c = 1.0, sn = 0.0;
-          if (fabs(apq) > thresh) jacobi_cs(app, aqq, apq, &c, &sn);
-          cs[(r + 1) & 1][lane] = make_double2(c, sn);
-        }
-        count += __popcll(m);
-      }
+      const double x11 = a[b11], x12 = a[b12], x21 = a[b21], x22 = a[b22];
+      // row factors of h: (c, -s) of a first slot, (s, c) of a second one; columns of l
+      const double ph = lane_shl(sn, c), qh = lane_shl(c, -sn);
+      const double pl = lane_shr(c, sn), ql = lane_shr(-sn, c);
+      double o12, o21, n1, n2;
+      rot_block(d1, od, od, d2, c, sn, c, sn, &n1, &o12, &o21, &n2);
+      slot_shift(k, &n1, &n2);
+      d1 = n1;
+      d2 = n2;
+      od = rot_entry(x11, x12, x21, x22, ph, qh, pl, ql);
+      jacobi_cs(d1, d2, od, thresh, &c, &sn);
+      if (lane < kHalf) cs[(r + 1) & 1][lane] = make_double2(c, sn);
+      count += sn != 0.0;
       __syncthreads();
     }
-    if (lane == 0) nrot_total = count;
-  } else if (wave >= 2) {
+    __builtin_amdgcn_s_setprio(0);
+    __syncthreads();
+    if (lane < kHalf && count > 0) atomicAdd(&nrot_total, count);
+  } else if (wave < 4) {
     // block (k1, k2), k1 >= k2, of the 16 x 16 pair blocks (136 of 192 threads)
-    const int idx = tid - 128;
+    const int idx = tid - 64;
     int k1 = 0, k2 = 0;
     {
       int rem = idx;
@@ -446,54 +456,45 @@ __device__ __forceinline__ void pair_solve_core(PairSmem& S, double mx, const do
               o12i = sym_idx(slot_next(f1), slot_next(s2)),
               o21i = sym_idx(slot_next(s1), slot_next(f2)),
               o22i = sym_idx(slot_next(s1), slot_next(s2));
+#pragma unroll 1
     for (int r = 0; r < kRounds; ++r) {
       if (active) {
         const double* a = buf[r & 1];
         double* o = buf[(r + 1) & 1];
         const double2 t1 = cs[r & 1][k1], t2 = cs[r & 1][k2];
+        const double x21 = a[i21];       // a pair's own block: entry (1, 2) is the same one
         double v11, v12, v21, v22;
-        if (k1 == k2) {
-          const double x21 = a[i21];
-          rot_block(a[i11], x21, x21, a[i22], t1.x, t1.y, t1.x, t1.y, &v11, &v12, &v21, &v22);
-          o[o11i] = v11;
-          o[o22i] = v22;
-          o[o21i] = t1.y != 0.0 ? 0.0 : x21;
-        } else {
-          rot_block(a[i11], a[i12], a[i21], a[i22], t1.x, t1.y, t2.x, t2.y, &v11, &v12, &v21,
-                    &v22);
-          o[o11i] = v11;
-          o[o12i] = v12;
-          o[o21i] = v21;
-          o[o22i] = v22;
-        }
+        rot_block(a[i11], a[i12], x21, a[i22], t1.x, t1.y, t2.x, t2.y, &v11, &v12, &v21, &v22);
+        if (k1 == k2) v12 = v21 = t1.y != 0.0 ? 0.0 : x21;
+        o[o11i] = v11;
+        o[o12i] = v12;
+        o[o21i] = v21;
+        o[o22i] = v22;
       }
       __syncthreads();
     }
   } else {
-    double ur[JP];
-#pragma unroll
-    for (int j = 0; j < JP; ++j) ur[j] = (j == lane) ? 1.0 : 0.0;
-#pragma unroll
+    // rows i and i + JP / 2 of U, columns by slot (after kRounds shifts slot = index)
+    const int i = 4 * (wave - 4) + (lane >> 4);
+    double ua1 = i == k, ua2 = 0.0, ub1 = 0.0, ub2 = i + kHalf == JP - 1 - k;
+#pragma unroll 1
     for (int r = 0; r < kRounds; ++r) {
-      if (lane < JP) {
-#pragma unroll
-        for (int k = 0; k < kHalf; ++k) {
-          // indices in slots k and JP-1-k at round r
-          const int p = (k == 0) ? 0 : 1 + (k - 1 + r) % (JP - 1);
-          const int q = 1 + (JP - 2 - k + r) % (JP - 1);
-          const double2 t = cs[r & 1][k];
-          const double up = ur[p], uq = ur[q];
-          ur[p] = fma(t.x, up, -(t.y * uq));
-          ur[q] = fma(t.y, up, t.x * uq);
-        }
-      }
+      const double2 t = cs[r & 1][k];
+      const double na1 = fma(t.x, ua1, -(t.y * ua2)), na2 = fma(t.y, ua1, t.x * ua2);
+      const double nb1 = fma(t.x, ub1, -(t.y * ub2)), nb2 = fma(t.y, ub1, t.x * ub2);
+      ua1 = na1;
+      ua2 = na2;
+      ub1 = nb1;
+      ub2 = nb2;
+      slot_shift(k, &ua1, &ua2);
+      slot_shift(k, &ub1, &ub2);
       __syncthreads();
     }
-    // row `lane` of U into LDS (the subproblem itself is no longer needed)
-    if (lane < JP) {
-#pragma unroll
-      for (int j = 0; j < JP; ++j) buf[0][lane + j * LDJ] = ur[j];
-    }
+    // into LDS (the subproblem itself is no longer needed)
+    buf[0][i + k * LDJ] = ua1;
+    buf[0][i + (JP - 1 - k) * LDJ] = ua2;
+    buf[0][i + kHalf + k * LDJ] = ub1;
+    buf[0][i + kHalf + (JP - 1 - k) * LDJ] = ub2;
   }
   __syncthreads();
   for (int idx = tid; idx < JP * JP; idx += kPairThreads) {
