@@ -702,7 +702,7 @@ chfsi_status dense_product(chfsi_ctx* c, const FilterProduct& d, int* packed) {
   hipEvent_t e0, e1;
   CK(prof_pair(c, &e0, &e1));
   if (e0) CK(hipEventRecord(e0, c->stream));
-  CK(filter_product(d, c->stream, c->ws, -1, filter_gemm_splits(), packed));
+  CK(filter_product(d, c->stream, c->ws, filter_gemm_splits(), packed));
   if (e1) CK(hipEventRecord(e1, c->stream));
   return CHFSI_OK;
 }

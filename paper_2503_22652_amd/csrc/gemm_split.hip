@@ -202,11 +202,12 @@ __device__ __forceinline__ f32x4 load4(const float* p, int left) {
     if (i < left) v[i] = p[i];
   return v;
 }
+// (an absent operand counts as zero, with no branch around its value's use)
 __device__ __forceinline__ EpiRegs epi_load(const Epilogue<float>& e, int m, int c, int left) {
-  EpiRegs r;
+  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+  EpiRegs r = {zero, zero, zero, e.delta};
   if (e.C1) r.c1 = load4(e.C1 + m + c * e.ldc1, left);
   if (e.C2) r.c2 = load4(e.C2 + m + c * e.ldc2, left);
-  r.f3 = e.delta;
   if (e.C3) {
     r.c3 = load4(e.C3 + m + c * e.ldc3, left);
     if (e.colscale3) r.f3 *= e.colscale3[c];
@@ -217,9 +218,9 @@ __device__ __forceinline__ f32x4 epi_value(const Epilogue<float>& e, const EpiRe
                                            int left) {
   f32x4 v = e.alpha * s;
   if (e.rowscale) v *= load4(e.rowscale + m, left);
-  if (e.C1) v += e.beta * r.c1;
-  if (e.C2) v += e.gamma * r.c2;
-  if (e.C3) v += r.f3 * r.c3;
+  v += e.beta * r.c1;
+  v += e.gamma * r.c2;
+  v += r.f3 * r.c3;
   return v;
 }
 __device__ __forceinline__ void store4(float* p, f32x4 v, int left) {
@@ -440,9 +441,11 @@ __global__ __launch_bounds__(256, 2) void k_step_large(StepArgs a) {
 // tile; its eight waves take the k-slices in turn (both operands packed, straight
 // from L2), add their partial tiles through LDS in wave order, and four of them
 // apply the epilogue, whose operands were requested first, and pack the next
-// step's right operand into the other of two buffers.  Latency bounds it: 512 x 48
-// in FP32 takes 9.3 us a step, against 20.9 for an FP32 matrix product and its
-// split-K reduction.  (16 waves, or 16 x 16 tiles for more workgroups: 9.6 and 11.2.)
+// step's right operand into the other of two buffers.  L2 latency and the launch bound
+// it: 1024 x 80 in FP32 takes 8.0 us a step, against 16.7 in two launches.  (More
+// slices in flight per wave change nothing.)  A branch around the use of an absent
+// operand made the compiler keep the arguments in LDS, at an address that needs the
+// dispatch packet in host memory: 14.3 us.
 // ---------------------------------------------------------------------------
 template <int P>
 __global__ __launch_bounds__(512) void k_step_small(StepArgs a, int pack) {
@@ -479,9 +482,9 @@ __global__ __launch_bounds__(512) void k_step_small(StepArgs a, int pack) {
     }
     return r;
   };
-  f32x16 acc;
+  f32x16 acc, low;                                 // P = 3: x0 y0, and the five small terms
 #pragma unroll
-  for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+  for (int i = 0; i < 16; ++i) acc[i] = low[i] = 0.f;
   auto compute = [&](const Slice& r) __attribute__((always_inline)) {
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
@@ -493,9 +496,11 @@ __global__ __launch_bounds__(512) void k_step_small(StepArgs a, int pack) {
 #pragma unroll
       for (int q = P - 1; q >= 0; --q)
 #pragma unroll
-        for (int p = P - 1 - q; p >= 0; --p)
-          acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-              af[p], __builtin_bit_cast(bf16x8, r.y[u][q]), acc, 0, 0, 0);
+        for (int p = P - 1 - q; p >= 0; --p) {
+          f32x16& into = p + q == 0 ? acc : low;
+          into = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+              af[p], __builtin_bit_cast(bf16x8, r.y[u][q]), into, 0, 0, 0);
+        }
     }
   };
   // (slices past n, which fill up a segment for the large path, hold nothing)
@@ -509,6 +514,7 @@ __global__ __launch_bounds__(512) void k_step_small(StepArgs a, int pack) {
     }
     compute(cur);
   }
+  if constexpr (P == 3) acc += low;
 #pragma unroll
   for (int g = 0; g < 4; ++g)
     red[wave][g][lane] = f32x4{acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3]};
@@ -591,7 +597,7 @@ size_t filter_product_bytes(int64_t n, int64_t N, int nseg, int planes) {
 }
 
 hipError_t filter_product(const FilterProduct& d, hipStream_t st, const Workspace& ws,
-                          int force_path, int force_splits, int* packed) {
+                          int force_splits, int* packed) {
   const int was_packed = *packed;
   *packed = 0;
   if (d.n <= 0 || d.N <= 0) return hipSuccess;
@@ -625,14 +631,14 @@ hipError_t filter_product(const FilterProduct& d, hipStream_t st, const Workspac
   int splits = force_splits > 0 ? force_splits : int(std::max<int64_t>(1, 512 / tiles));
   splits = std::min(splits, std::max(1, a.slices / 8));
   splits = int(std::min<size_t>(splits, (ws.bytes - pbytes) / (size_t(d.n) * d.N * sizeof(float))));
-  // one launch below this much work (n N slices): its waves wait on L2 latency and
-  // re-read the operands per 32 x 32 tile, but the second launch and the partials'
-  // round trip are saved.  Measured, us a step, one launch / two: three planes
-  // 512 x 48 9.3 / 13.5, 1024 x 80 14.4 / 16.5, 1536 x 96 (7.1e6) 19.1 / 18.4, 2048 x
-  // 144 33.0 / 26.3; one plane 512 x 48 (0.4e6) 8.5 / 9.3, 1024 x 80 (2.6e6) 11.9 / 11.3,
-  // 2048 x 144 20.6 / 17.7
-  bool large = splits > 0 && double(d.n) * d.N * a.slices >= (d.planes == 3 ? 7e6 : 1.5e6);
-  if (force_path >= 0) large = splits > 0 && force_path > 0;
+  // one launch below this much work (n N slices): it re-reads the operands per 32 x 32
+  // tile, but the second launch and the partials' round trip are saved.  Measured, us a
+  // step, one launch / two: three planes 1024 x 80 (2.6e6) 8.0 / 16.7, 2048 x 144 20.1 /
+  // 26.7, 3072 x 160 (4.7e7) 28.5 / 40.9, 4096 x 144 (7.5e7) 51.3 / 49.3, 8192 x 64 (1.3e8)
+  // 90.6 / 71.1; one plane 1024 x 80 6.3 / 11.1, 4096 x 144 21.0 / 24.9, 8192 x 64 27.3 /
+  // 31.4, 4096 x 272 (1.4e8) 31.7 / 31.3, 8192 x 128 (2.7e8) 52.6 / 38.9
+  const bool large = splits > 0 && (force_splits > 0 || double(d.n) * d.N * a.slices >=
+                                                             (d.planes == 3 ? 7e7 : 1.4e8));
   const dim3 grid32(unsigned(a.sps), unsigned(c32));
   const int pack = d.pack_next ? 1 : 0;
   if (!was_packed) {

@@ -142,9 +142,9 @@ struct FilterProduct {
 size_t filter_product_bytes(int64_t n, int64_t N, int nseg, int planes);
 // *packed: 0, or what the step before (with pack_next, nothing having used ws
 // since) left there: the workspace then holds this step's right operand.
-// force_path (-1: by size) 1: split-K over workgroups and a reduction, 0: one launch.
+// force_splits > 0: two launches (products over that many k-splits, and a reduction).
 hipError_t filter_product(const FilterProduct& d, hipStream_t st, const Workspace& ws,
-                          int force_path, int force_splits, int* packed);
+                          int force_splits, int* packed);
 
 // Which tile configuration/split the heuristic picks (for reports and tests).
 template <typename T>

@@ -22,7 +22,7 @@ import paper_2503_22652_amd as P  # noqa: E402
 
 DEG = 4
 # (n, b): one element past and short of tiles, slices and stages; odd leading
-# dimensions; one launch, then (from 700 x 100 BF16, 1300 x 163 FP32) two
+# dimensions; all in one launch a step
 SIZES = [(20, 1), (31, 4), (32, 32), (33, 31), (64, 33), (65, 2), (127, 16), (129, 65), (700, 100),
          (1300, 163), (1281, 321)]
 
@@ -89,3 +89,19 @@ def test_filter_product_non_finite_stays_in_its_column(n, b):
     good = [j for j in range(b) if j not in (3, 11)]
     assert np.array_equal(a[:, good], c[:, good])
     assert not np.isfinite(c[:, 3]).any() and not np.isfinite(c[:, 11]).any()
+
+
+@pytest.mark.parametrize("n,b", [(33, 31), (129, 65), (700, 100), (1281, 321)])
+@pytest.mark.parametrize("splits", [1, 3])
+@pytest.mark.parametrize("cplx", [False, True], ids=["real", "complex"])
+@pytest.mark.parametrize("prec", [P.PREC_FP32, P.PREC_BF16])
+def test_filter_product_edges_two_launches(monkeypatch, prec, cplx, splits, n, b):
+    """The path of large products (k-splits and a reduction) at ragged sizes."""
+    monkeypatch.setenv("CHFSI_FILTER_GEMM_SPLITS", str(splits))
+    test_filter_product_edges(prec, cplx, n, b)
+
+
+@pytest.mark.parametrize("n,b,prec", [(3000, 255, P.PREC_FP32), (3000, 540, P.PREC_BF16)])
+def test_filter_product_large_by_rule(prec, n, b):
+    """Past the size from which a step is two launches."""
+    test_filter_product_edges(prec, False, n, b)
