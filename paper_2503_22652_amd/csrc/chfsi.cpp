@@ -752,14 +752,18 @@ chfsi_status filter_rchfsi(chfsi_ctx* c, const double* X, int64_t ldx, const dou
   const int nsteps = p - 1;
   const double scale1 = f.sigma1 / f.e;
   double fl = 0.0;
-  const bool dense = c->A.kind == CHFSI_OP_DENSE;
+  const bool dense = c->A.kind == CHFSI_OP_DENSE, csr = c->A.kind == CHFSI_OP_CSR;
   if (c->prm.filter_prec == CHFSI_PREC_FP32 || (c->prm.filter_prec == CHFSI_PREC_BF16 && dense)) {
     // FP32 filter blocks; the operator product is FP32 MFMA, or BF16 MFMA on
     // the bfloat16 copy of A (dense BF16)
     float* RX = c->f32_a;
     float* RY = c->f32_b;
     float* Yc = c->f32_c;
-    CK(rchfsi_init_f32(resid, ldr, n, b, scale1, RY, RX, Yc, n, c->stream));
+    if (csr)
+      CK(csr_rchfsi_init(csr_of(c, c->A, true), CHFSI_PREC_FP32, resid, ldr, b, scale1, RY, RX, Yc,
+                         c->stream));
+    else
+      CK(rchfsi_init_f32(resid, ldr, n, b, scale1, RY, RX, Yc, n, c->stream));
     int packed = 0;   // dense: each step leaves the next one's right operand in the workspace
     for (int s = 0; s < nsteps; ++s) {
       const StepCoef sp = next_step();
@@ -796,7 +800,7 @@ chfsi_status filter_rchfsi(chfsi_ctx* c, const double* X, int64_t ldx, const dou
           hipEvent_t e0, e1;
           CK(prof_pair(c, &e0, &e1));
           if (e0) CK(hipEventRecord(e0, c->stream));
-          if (c->A.kind == CHFSI_OP_CSR)
+          if (csr)
             CK(csr_rchfsi_step_f32(csr_of(c, c->A, true), c->dinv ? c->dinv32 : nullptr, RY, RX,
                                    Yc, c->coef32 + int64_t(s) * b, ss, b, c->stream));
           else
@@ -808,11 +812,19 @@ chfsi_status filter_rchfsi(chfsi_ctx* c, const double* X, int64_t ldx, const dou
       }
       std::swap(RX, RY);
     }
-    CK(rchfsi_reconstruct_f32(RY, n, c->dinv, X, ldx, c->lamY, Yp, ldy, n, b, c->stream));
+    if (csr)
+      CK(csr_rchfsi_reconstruct(csr_of(c, c->A, true), CHFSI_PREC_FP32, RY, c->dinv, X, ldx, c->lamY,
+                                Yp, ldy, b, c->stream));
+    else
+      CK(rchfsi_reconstruct_f32(RY, n, c->dinv, X, ldx, c->lamY, Yp, ldy, n, b, c->stream));
   } else if (c->prm.filter_prec == CHFSI_PREC_FP64) {
     double* RX = c->f64_a;
     double* RY = c->f64_b;
-    CK(rchfsi_init_f64(resid, ldr, n, b, scale1, RY, RX, n, c->stream));
+    if (csr)
+      CK(csr_rchfsi_init(csr_of(c, c->A, false), CHFSI_PREC_FP64, resid, ldr, b, scale1, RY, RX,
+                         nullptr, c->stream));
+    else
+      CK(rchfsi_init_f64(resid, ldr, n, b, scale1, RY, RX, n, c->stream));
     for (int s = 0; s < nsteps; ++s) {
       const StepCoef sp = next_step();
       if (dense) {
@@ -849,7 +861,7 @@ chfsi_status filter_rchfsi(chfsi_ctx* c, const double* X, int64_t ldx, const dou
           hipEvent_t e0, e1;
           CK(prof_pair(c, &e0, &e1));
           if (e0) CK(hipEventRecord(e0, c->stream));
-          if (c->A.kind == CHFSI_OP_CSR)
+          if (csr)
             CK(csr_rchfsi_step_f64(csr_of(c, c->A, false), c->dinv, RY, RX, resid, ldr,
                                    c->coef64 + int64_t(s) * b, ss, b, c->stream));
           else
@@ -861,13 +873,21 @@ chfsi_status filter_rchfsi(chfsi_ctx* c, const double* X, int64_t ldx, const dou
       }
       std::swap(RX, RY);
     }
-    CK(rchfsi_reconstruct_f64(RY, n, c->dinv, X, ldx, c->lamY, Yp, ldy, n, b, c->stream));
+    if (csr)
+      CK(csr_rchfsi_reconstruct(csr_of(c, c->A, false), CHFSI_PREC_FP64, RY, c->dinv, X, ldx,
+                                c->lamY, Yp, ldy, b, c->stream));
+    else
+      CK(rchfsi_reconstruct_f64(RY, n, c->dinv, X, ldx, c->lamY, Yp, ldy, n, b, c->stream));
   } else {
     // BF16-stored blocks, FP32 arithmetic (stencil operators)
     void* RX = c->bf_a;
     void* RY = c->bf_b;
     void* Yc = c->bf_c;
-    CK(rchfsi_init_bf16(resid, ldr, n, b, scale1, RY, RX, Yc, c->stream));
+    if (csr)
+      CK(csr_rchfsi_init(csr_of(c, c->A, true), CHFSI_PREC_BF16, resid, ldr, b, scale1, RY, RX, Yc,
+                         c->stream));
+    else
+      CK(rchfsi_init_bf16(resid, ldr, n, b, scale1, RY, RX, Yc, c->stream));
     for (int s = 0; s < nsteps; ++s) {
       const StepCoef sp = next_step();
       StencilStep ss{sp.a, sp.bb, sp.cc, sp.a};
@@ -875,7 +895,7 @@ chfsi_status filter_rchfsi(chfsi_ctx* c, const double* X, int64_t ldx, const dou
         hipEvent_t e0, e1;
         CK(prof_pair(c, &e0, &e1));
         if (e0) CK(hipEventRecord(e0, c->stream));
-        if (c->A.kind == CHFSI_OP_CSR)
+        if (csr)
           CK(csr_rchfsi_step_bf16(csr_of(c, c->A, true), c->dinv ? c->dinv32 : nullptr, RY, RX,
                                   Yc, c->coef32 + int64_t(s) * b, ss, b, c->stream));
         else
@@ -886,7 +906,11 @@ chfsi_status filter_rchfsi(chfsi_ctx* c, const double* X, int64_t ldx, const dou
       fl += op_flops(c->A) * double(n) * double(b);
       std::swap(RX, RY);
     }
-    CK(rchfsi_reconstruct_bf16(RY, c->dinv, X, ldx, c->lamY, Yp, ldy, n, b, c->stream));
+    if (csr)
+      CK(csr_rchfsi_reconstruct(csr_of(c, c->A, true), CHFSI_PREC_BF16, RY, c->dinv, X, ldx,
+                                c->lamY, Yp, ldy, b, c->stream));
+    else
+      CK(rchfsi_reconstruct_bf16(RY, c->dinv, X, ldx, c->lamY, Yp, ldy, n, b, c->stream));
   }
   if (flops) *flops += fl;
   return CHFSI_OK;

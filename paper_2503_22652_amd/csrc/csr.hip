@@ -14,6 +14,14 @@
 // For the residual filter's A (D^{-1} R_Y), D^{-1} is folded into the staged
 // values (column side).  Rows longer than kLdsKmax use a plain kernel with one
 // thread per (row, column).
+//
+// The gathers bound that sweep: 64^3 grid, 27 entries a row, 64 FP32 columns took 153 us
+// a step.  The residual filter therefore keeps its blocks in groups of G columns of 16
+// bytes a row, element (i, j) at (j / G * n + i) G + j % G and the last b % G columns
+// column by column: a gather is then one aligned 16-byte load for G columns and the
+// addresses and staged entries are shared.  113 us a step, 93 of them the L1 lookups (two
+// per 64 bytes for a row's shifted neighbours).  128- and 256-row tiles, whose gathers
+// could share lines in L1, take 124 and 134 us; round-robin tiles over the XCDs 127.
 #include "internal.h"
 #include "stencil_api.h"
 
@@ -62,6 +70,13 @@ struct CsrArgs {
   AT alpha, beta, gamma, delta;
 };
 
+// workgroups go round-robin over the 8 XCDs: neighbouring tiles, which share source
+// entries, on one XCD
+__device__ __forceinline__ int64_t xcd_unit(int64_t h, int64_t total) {
+  const int64_t xcd = h & 7, slot = h >> 3, full = total >> 3, rem = total & 7;
+  return xcd < rem ? xcd * (full + 1) + slot : rem * (full + 1) + (xcd - rem) * full + slot;
+}
+
 template <typename S, typename AT, typename VT, int MODE>
 __device__ __forceinline__ void epilogue(const CsrArgs<S, AT, VT>& a, int64_t row, int64_t j,
                                          AT acc) {
@@ -86,7 +101,7 @@ __global__ __launch_bounds__(kThreads) void k_csr_tile(CsrArgs<S, AT, VT> a) {
   const int kmax = a.kmax;
   int32_t* lc = reinterpret_cast<int32_t*>(smem);
   VT* lv = reinterpret_cast<VT*>(smem + ((size_t(kmax) * kRows * sizeof(int32_t) + 15) & ~size_t(15)));
-  const int64_t row0 = int64_t(blockIdx.x) * kRows;
+  const int64_t row0 = xcd_unit(blockIdx.x, gridDim.x) * kRows;
   for (int idx = threadIdx.x; idx < kmax * kRows; idx += kThreads) {
     const int r = idx & (kRows - 1), k = idx / kRows;
     const int64_t row = row0 + r;
@@ -114,6 +129,174 @@ __global__ __launch_bounds__(kThreads) void k_csr_tile(CsrArgs<S, AT, VT> a) {
     for (int k = 0; k < kmax; ++k)
       acc += AT(lv[k * kRows + lane]) * load_as(sj, lc[k * kRows + lane], AT());
     epilogue<S, AT, VT, MODE>(a, row, j, acc);
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Residual-filter blocks in groups of columns
+// ---------------------------------------------------------------------------
+template <typename S>
+constexpr int kGroup = 16 / int(sizeof(S));
+template <typename S>
+struct GroupOf {
+  typedef S type __attribute__((ext_vector_type(16 / sizeof(S))));
+};
+
+// element (i, j)
+template <typename S>
+__device__ __forceinline__ int64_t group_index(int64_t i, int64_t j, int64_t n, int64_t b) {
+  constexpr int G = kGroup<S>;
+  const int64_t full = b / G * G;
+  return j < full ? (j / G * n + i) * G + j % G : j * n + i;
+}
+
+// the filter's start: RY = scale R, RX = 0 and (Yc given) Yc = R
+template <typename S, typename AT>
+__global__ __launch_bounds__(kThreads) void k_csr_init(const double* R, int64_t ldr, int64_t n,
+                                                       int64_t b, double scale, S* RY, S* RX, S* Yc) {
+  constexpr int G = kGroup<S>;
+  typedef typename GroupOf<S>::type V;
+  const int64_t ng = b / G, items = n * (ng + b % G);
+  for (int64_t idx = int64_t(blockIdx.x) * kThreads + threadIdx.x; idx < items;
+       idx += int64_t(gridDim.x) * kThreads) {
+    const int64_t q = idx / n, i = idx - q * n;
+    if (q < ng) {
+      V y, z, r;
+#pragma unroll
+      for (int c = 0; c < G; ++c) {
+        const double v = R[i + (q * G + c) * ldr];
+        S t;
+        store_to(&t, 0, AT(scale * v));
+        y[c] = t;
+        store_to(&t, 0, AT(v));
+        r[c] = t;
+        z[c] = S(0);
+      }
+      reinterpret_cast<V*>(RY)[idx] = y;
+      reinterpret_cast<V*>(RX)[idx] = z;
+      if (Yc) reinterpret_cast<V*>(Yc)[idx] = r;
+    } else {
+      const int64_t j = ng * G + (q - ng), at = j * n + i;
+      const double v = R[i + j * ldr];
+      store_to(RY, at, AT(scale * v));
+      store_to(RX, at, AT(0));
+      if (Yc) store_to(Yc, at, AT(v));
+    }
+  }
+}
+
+// the filter's end: Yp = D^{-1} RY + X Lambda_Y
+template <typename S, typename AT>
+__global__ __launch_bounds__(kThreads) void k_csr_reconstruct(const S* RY, const double* dinv,
+                                                              const double* X, int64_t ldx,
+                                                              const double* lamY, double* Yp,
+                                                              int64_t ldy, int64_t n, int64_t b) {
+  constexpr int G = kGroup<S>;
+  typedef typename GroupOf<S>::type V;
+  const int64_t ng = b / G, items = n * (ng + b % G);
+  for (int64_t idx = int64_t(blockIdx.x) * kThreads + threadIdx.x; idx < items;
+       idx += int64_t(gridDim.x) * kThreads) {
+    const int64_t q = idx / n, i = idx - q * n;
+    const bool group = q < ng;
+    const int64_t j0 = group ? q * G : ng * G + (q - ng);
+    V y;
+    if (group)
+      y = reinterpret_cast<const V*>(RY)[idx];
+    else
+      y[0] = RY[j0 * n + i];
+#pragma unroll
+    for (int c = 0; c < G; ++c) {
+      if (c > 0 && !group) break;
+      const S t = y[c];
+      double r = double(load_as(&t, 0, AT()));
+      if (dinv) r *= dinv[i];
+      Yp[i + (j0 + c) * ldy] = r + X[i + (j0 + c) * ldx] * lamY[j0 + c];
+    }
+  }
+}
+
+// The step RX <- alpha A (D^{-1} RY) + beta RY + gamma RX + delta colcoef[j] Yf on such
+// blocks (forc with ldf >= 0: column-major).  `parts` workgroups share a tile's columns.
+template <typename S, typename AT, typename VT>
+__global__ __launch_bounds__(kThreads) void k_csr_group(CsrArgs<S, AT, VT> a, int parts) {
+  constexpr int G = kGroup<S>, CW = kThreads / kRows;
+  typedef typename GroupOf<S>::type V;
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int kmax = a.kmax;
+  uint32_t* lo = reinterpret_cast<uint32_t*>(smem);          // byte offset of a row's group
+  VT* lv = reinterpret_cast<VT*>(smem + size_t(kmax) * kRows * sizeof(uint32_t));
+  const int64_t unit = xcd_unit(blockIdx.x, gridDim.x), row0 = unit / parts * kRows;
+  {
+    const int r = threadIdx.x % kRows;
+    const int64_t row = row0 + r;
+    const int64_t s = row < a.n ? a.rowptr[row] : 0, e = row < a.n ? a.rowptr[row + 1] : 0;
+#pragma unroll 4
+    for (int k = threadIdx.x / kRows; k < kmax; k += CW) {
+      int32_t c = row < a.n ? int32_t(row) : 0;   // padding: this row's own index with weight 0
+      VT v = VT(0);
+      if (k < e - s) {
+        c = a.col[s + k];
+        v = a.val[s + k];
+        if (a.cdinv) v = VT(AT(v) * a.cdinv[c]);
+      }
+      lo[k * kRows + r] = uint32_t(c) * 16u;
+      lv[k * kRows + r] = v;
+    }
+  }
+  __syncthreads();
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t row = row0 + lane;
+  if (row >= a.n) return;   // no barrier follows
+  lo += lane;
+  lv += lane;
+  const int64_t ng = a.b / G, first = unit % parts * CW + wave;
+  const int64_t step = int64_t(parts) * CW;
+  for (int64_t q = first; q < ng; q += step) {
+    const char* src = reinterpret_cast<const char*>(reinterpret_cast<const V*>(a.src) + q * a.n);
+    const int64_t at = q * a.n + row;
+    const V s = reinterpret_cast<const V*>(a.src)[at], p = reinterpret_cast<const V*>(a.prev)[at];
+    V f;
+    if (a.ldf < 0)
+      f = reinterpret_cast<const V*>(a.forc)[at];
+    else
+#pragma unroll
+      for (int c = 0; c < G; ++c) f[c] = a.forc[row + (q * G + c) * a.ldf];
+    AT acc[G];
+#pragma unroll
+    for (int c = 0; c < G; ++c) acc[c] = AT(0);
+#pragma unroll 9
+    for (int k = 0; k < kmax; ++k) {
+      const AT v = AT(lv[k * kRows]);
+      const V x = *reinterpret_cast<const V*>(src + lo[k * kRows]);
+#pragma unroll
+      for (int c = 0; c < G; ++c) {
+        const S t = x[c];
+        acc[c] += v * load_as(&t, 0, AT());
+      }
+    }
+    V out;
+#pragma unroll
+    for (int c = 0; c < G; ++c) {
+      const S ts = s[c], tp = p[c], tf = f[c];
+      S to;
+      store_to(&to, 0, a.alpha * acc[c] + a.beta * load_as(&ts, 0, AT()) +
+                           a.gamma * load_as(&tp, 0, AT()) +
+                           a.delta * a.colcoef[q * G + c] * load_as(&tf, 0, AT()));
+      out[c] = to;
+    }
+    reinterpret_cast<V*>(a.dst)[at] = out;
+  }
+  for (int64_t j = ng * G + first; j < a.b; j += step) {
+    const S* sj = a.src + j * a.n;
+    AT acc = AT(0);
+#pragma unroll 9
+    for (int k = 0; k < kmax; ++k)
+      acc += AT(lv[k * kRows]) * load_as(sj, lo[k * kRows] / 16u, AT());
+    const int64_t at = j * a.n + row;
+    store_to(a.dst, at, a.alpha * acc + a.beta * load_as(sj, row, AT()) +
+                            a.gamma * load_as(a.prev, at, AT()) +
+                            a.delta * a.colcoef[j] *
+                                load_as(a.forc, a.ldf < 0 ? at : row + j * a.ldf, AT()));
   }
 }
 
@@ -176,6 +359,34 @@ hipError_t launch(const CsrArgs<S, AT, VT>& a, hipStream_t st) {
   return hipGetLastError();
 }
 
+// blocks in groups: rows short enough to stage, 32-bit byte offsets
+bool grouped(const CsrMat& A) {
+  return A.kmax <= kLdsKmax && A.n <= int64_t(0xffffffff) / 16;
+}
+
+// one residual-filter step on the layout of csr_rchfsi_init
+template <typename S, typename AT, typename VT>
+hipError_t launch_rstep(CsrArgs<S, AT, VT> a, bool group, hipStream_t st) {
+  if (a.n <= 0 || a.b <= 0) return hipSuccess;
+  if (!group) {
+    if (a.ldf < 0) a.ldf = a.n;
+    return launch<S, AT, VT, MODE_RSTEP>(a, st);
+  }
+  a.kmax = std::max(a.kmax, 1);
+  const size_t lds = size_t(a.kmax) * kRows * (sizeof(uint32_t) + sizeof(VT));
+  const int64_t tiles = (a.n + kRows - 1) / kRows;
+  // few tiles: columns split over workgroups, down to a group a wave, up to four a CU
+  const int64_t units = a.b / kGroup<S> + a.b % kGroup<S>;
+  const int parts = int(std::max<int64_t>(1, std::min((units + 3) / 4, 1024 / tiles)));
+  if (tiles * parts > 0x7fffffff) return hipErrorInvalidValue;
+  k_csr_group<S, AT, VT><<<dim3(unsigned(tiles * parts)), kThreads, lds, st>>>(a, parts);
+  return hipGetLastError();
+}
+
+inline unsigned grid_for(int64_t items) {
+  return unsigned(std::max<int64_t>(1, std::min<int64_t>((items + kThreads - 1) / kThreads, 65536)));
+}
+
 template <typename S, typename AT, typename VT>
 CsrArgs<S, AT, VT> base_args(const CsrMat& A, int64_t b) {
   CsrArgs<S, AT, VT> a{};
@@ -215,6 +426,57 @@ hipError_t csr_apply_f64(const CsrMat& A, const double* X, int64_t ldx, double* 
   return launch<double, double, double, MODE_APPLY>(a, st);
 }
 
+hipError_t csr_rchfsi_init(const CsrMat& A, int prec, const double* R, int64_t ldr, int64_t b,
+                           double scale, void* RY, void* RX, void* Yc, hipStream_t st) {
+  const int64_t n = A.n;
+  if (!grouped(A)) {
+    if (prec == CHFSI_PREC_FP64)
+      return rchfsi_init_f64(R, ldr, n, b, scale, static_cast<double*>(RY), static_cast<double*>(RX),
+                             n, st);
+    if (prec == CHFSI_PREC_FP32)
+      return rchfsi_init_f32(R, ldr, n, b, scale, static_cast<float*>(RY), static_cast<float*>(RX),
+                             static_cast<float*>(Yc), n, st);
+    return rchfsi_init_bf16(R, ldr, n, b, scale, RY, RX, Yc, st);
+  }
+  if (prec == CHFSI_PREC_FP64)
+    k_csr_init<double, double><<<grid_for(n * b / 2), kThreads, 0, st>>>(
+        R, ldr, n, b, scale, static_cast<double*>(RY), static_cast<double*>(RX), nullptr);
+  else if (prec == CHFSI_PREC_FP32)
+    k_csr_init<float, float><<<grid_for(n * b / 4), kThreads, 0, st>>>(
+        R, ldr, n, b, scale, static_cast<float*>(RY), static_cast<float*>(RX),
+        static_cast<float*>(Yc));
+  else
+    k_csr_init<uint16_t, float><<<grid_for(n * b / 8), kThreads, 0, st>>>(
+        R, ldr, n, b, scale, static_cast<uint16_t*>(RY), static_cast<uint16_t*>(RX),
+        static_cast<uint16_t*>(Yc));
+  return hipGetLastError();
+}
+
+hipError_t csr_rchfsi_reconstruct(const CsrMat& A, int prec, const void* RY, const double* dinv,
+                                  const double* X, int64_t ldx, const double* lamY, double* Yp,
+                                  int64_t ldy, int64_t b, hipStream_t st) {
+  const int64_t n = A.n;
+  if (!grouped(A)) {
+    if (prec == CHFSI_PREC_FP64)
+      return rchfsi_reconstruct_f64(static_cast<const double*>(RY), n, dinv, X, ldx, lamY, Yp, ldy,
+                                    n, b, st);
+    if (prec == CHFSI_PREC_FP32)
+      return rchfsi_reconstruct_f32(static_cast<const float*>(RY), n, dinv, X, ldx, lamY, Yp, ldy,
+                                    n, b, st);
+    return rchfsi_reconstruct_bf16(RY, dinv, X, ldx, lamY, Yp, ldy, n, b, st);
+  }
+  if (prec == CHFSI_PREC_FP64)
+    k_csr_reconstruct<double, double><<<grid_for(n * b / 2), kThreads, 0, st>>>(
+        static_cast<const double*>(RY), dinv, X, ldx, lamY, Yp, ldy, n, b);
+  else if (prec == CHFSI_PREC_FP32)
+    k_csr_reconstruct<float, float><<<grid_for(n * b / 4), kThreads, 0, st>>>(
+        static_cast<const float*>(RY), dinv, X, ldx, lamY, Yp, ldy, n, b);
+  else
+    k_csr_reconstruct<uint16_t, float><<<grid_for(n * b / 8), kThreads, 0, st>>>(
+        static_cast<const uint16_t*>(RY), dinv, X, ldx, lamY, Yp, ldy, n, b);
+  return hipGetLastError();
+}
+
 hipError_t csr_rchfsi_step_f64(const CsrMat& A, const double* dinv, const double* RY, double* RX,
                                const double* Yf, int64_t ldf, const double* colcoef,
                                StencilStep s, int64_t b, hipStream_t st) {
@@ -227,13 +489,13 @@ hipError_t csr_rchfsi_step_f64(const CsrMat& A, const double* dinv, const double
   a.prev = RX;
   a.ldp = A.n;
   a.forc = Yf;
-  a.ldf = ldf;
+  a.ldf = ldf;              // the caller's residuals: column-major
   a.colcoef = colcoef;
   a.alpha = s.alpha;
   a.beta = s.beta;
   a.gamma = s.gamma;
   a.delta = s.delta;
-  return launch<double, double, double, MODE_RSTEP>(a, st);
+  return launch_rstep<double, double, double>(a, grouped(A), st);
 }
 
 template <typename S>
@@ -248,13 +510,13 @@ static hipError_t rstep_lowp(const CsrMat& A32, const float* dinv, const S* RY, 
   a.prev = RX;
   a.ldp = A32.n;
   a.forc = Yf;
-  a.ldf = A32.n;
+  a.ldf = -1;               // in the blocks' layout
   a.colcoef = colcoef;
   a.alpha = float(s.alpha);
   a.beta = float(s.beta);
   a.gamma = float(s.gamma);
   a.delta = float(s.delta);
-  return launch<S, float, float, MODE_RSTEP>(a, st);
+  return launch_rstep<S, float, float>(a, grouped(A32), st);
 }
 
 hipError_t csr_rchfsi_step_f32(const CsrMat& A32, const float* dinv, const float* RY, float* RX,

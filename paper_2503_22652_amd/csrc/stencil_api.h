@@ -116,7 +116,15 @@ hipError_t csr_check(const chfsi_operator& op, int* flags_dev, int* flags_host, 
 // Y = A X (FP64), column-major n x b blocks
 hipError_t csr_apply_f64(const CsrMat& A, const double* X, int64_t ldx, double* Y, int64_t ldy,
                          int64_t b, hipStream_t st);
-// residual-filter step (ld n): RX <- alpha A (dinv .* RY) + beta RY + gamma RX
+// The residual filter's blocks RY, RX and (FP32, BF16) Yc, n b elements each, in the
+// kernels' own layout between these: init sets RY = scale R, RX = 0, Yc = R;
+// reconstruct forms Yp = dinv .* RY + X Lambda_Y.  A's values are not read.
+hipError_t csr_rchfsi_init(const CsrMat& A, int prec, const double* R, int64_t ldr, int64_t b,
+                           double scale, void* RY, void* RX, void* Yc, hipStream_t st);
+hipError_t csr_rchfsi_reconstruct(const CsrMat& A, int prec, const void* RY, const double* dinv,
+                                  const double* X, int64_t ldx, const double* lamY, double* Yp,
+                                  int64_t ldy, int64_t b, hipStream_t st);
+// residual-filter step (f64: Yf column-major): RX <- alpha A (dinv .* RY) + beta RY + gamma RX
 //                                    + delta colcoef[j] Yf
 hipError_t csr_rchfsi_step_f64(const CsrMat& A, const double* dinv, const double* RY, double* RX,
                                const double* Yf, int64_t ldf, const double* colcoef,
