@@ -158,41 +158,48 @@ __global__ __launch_bounds__(kThreads) void k_copy(const double* __restrict__ in
   }
 }
 
-__global__ __launch_bounds__(kThreads) void k_gram_scale_vec(const double* __restrict__ G,
-                                                              int64_t ldg, int64_t b, double* s,
-                                                              int* bad) {
-  const int64_t j = blockIdx.x * int64_t(kThreads) + threadIdx.x;
-  if (j >= b) return;
-  const double d = G[j + j * ldg];
-  if (!(d > 0.0) || !isfinite(d)) {
-    atomicExch(bad, 1);
-    s[j] = 1.0;
-  } else {
-    s[j] = 1.0 / sqrt(d);
+// entry (i, j) of a symmetric matrix; lower: only the lower triangle holds it
+__device__ __forceinline__ double sym_entry(const double* G, int64_t ldg, int64_t i, int64_t j,
+                                            int lower) {
+  return lower && i < j ? G[j + i * ldg] : G[i + j * ldg];
+}
+
+// s = diag(G)^{-1/2} (1 and *bad = 1 where the diagonal is not positive and finite) and
+// s G s into Gs and Gc.  Every entry forms its own two factors: one small launch
+// instead of four (mirror, factors, scale, copy) at 2.5 to 5 us each.
+__global__ __launch_bounds__(kThreads) void k_scale_gram(const double* __restrict__ G, int64_t ldg,
+                                                          int64_t b, int lower, double* s, int* bad,
+                                                          double* Gs, double* Gc, int64_t lds) {
+  auto factor = [&](int64_t j, bool* ok) {
+    const double d = G[j + j * ldg];
+    *ok = d > 0.0 && isfinite(d);
+    return *ok ? 1.0 / sqrt(d) : 1.0;
+  };
+  const int64_t total = b * b;
+  for (int64_t idx = blockIdx.x * int64_t(kThreads) + threadIdx.x; idx < total;
+       idx += int64_t(gridDim.x) * kThreads) {
+    const int64_t j = idx / b, i = idx - j * b;
+    bool oi, oj;
+    const double si = factor(i, &oi), sj = factor(j, &oj);
+    const double v = si * sym_entry(G, ldg, i, j, lower) * sj;
+    Gs[i + j * lds] = v;
+    Gc[i + j * lds] = v;
+    if (i == j) {
+      s[j] = sj;
+      if (!oj) atomicExch(bad, 1);
+    }
   }
 }
 
 __global__ __launch_bounds__(kThreads) void k_scale_sym(const double* __restrict__ G, int64_t ldg,
-                                                         int64_t b, const double* __restrict__ s,
-                                                         double* out, int64_t ldo) {
+                                                         int64_t b, int lower,
+                                                         const double* __restrict__ s, double* out,
+                                                         int64_t ldo) {
   const int64_t total = b * b;
   for (int64_t idx = blockIdx.x * int64_t(kThreads) + threadIdx.x; idx < total;
        idx += int64_t(gridDim.x) * kThreads) {
     const int64_t j = idx / b, i = idx - j * b;
-    out[i + j * ldo] = s[i] * G[i + j * ldg] * s[j];
-  }
-}
-
-__global__ __launch_bounds__(kThreads) void k_symmetrize(double* A, int64_t lda, int64_t b) {
-  const int64_t total = b * b;
-  for (int64_t idx = blockIdx.x * int64_t(kThreads) + threadIdx.x; idx < total;
-       idx += int64_t(gridDim.x) * kThreads) {
-    const int64_t j = idx / b, i = idx - j * b;
-    if (i < j) {
-      const double v = 0.5 * (A[i + j * lda] + A[j + i * lda]);
-      A[i + j * lda] = v;
-      A[j + i * lda] = v;
-    }
+    out[i + j * ldo] = s[i] * sym_entry(G, ldg, i, j, lower) * s[j];
   }
 }
 
@@ -218,14 +225,16 @@ __global__ __launch_bounds__(kThreads) void k_symmetrize_panels(double* A, int64
   }
 }
 
-__global__ __launch_bounds__(kThreads) void k_scale_columns(double* M, int64_t ldm, int64_t n,
+// out = M diag(v) (out may be M)
+__global__ __launch_bounds__(kThreads) void k_scale_columns(const double* M, int64_t ldm,
+                                                             double* out, int64_t ldo, int64_t n,
                                                              int64_t b,
                                                              const double* __restrict__ v) {
   const int64_t total = n * b;
   for (int64_t idx = blockIdx.x * int64_t(kThreads) + threadIdx.x; idx < total;
        idx += int64_t(gridDim.x) * kThreads) {
     const int64_t j = idx / n, i = idx - j * n;
-    M[i + j * ldm] *= v[j];
+    out[i + j * ldo] = M[i + j * ldm] * v[j];
   }
 }
 
@@ -300,7 +309,33 @@ __global__ __launch_bounds__(kThreads) void k_check_finite(const double* __restr
     if (!isfinite(v[idx])) atomicExch(flag, 1);
 }
 
+// Ritz values and residual norms to the host (pinned memory, written by the kernel:
+// one launch instead of two checks and three copies), with the device's four flags, of
+// which [2] also tells a non-finite value
+__global__ __launch_bounds__(kThreads) void k_rr_report(const double* __restrict__ w,
+                                                         const double* __restrict__ norms, int64_t b,
+                                                         const int* flags, double* h_w,
+                                                         double* h_norms, int* h_flags) {
+  __shared__ int bad;
+  if (threadIdx.x == 0) bad = 0;
+  __syncthreads();
+  for (int64_t j = threadIdx.x; j < b; j += kThreads) {
+    const double x = w[j], y = norms[j];
+    if (!isfinite(x) || !isfinite(y)) bad = 1;
+    h_w[j] = x;
+    h_norms[j] = y;
+  }
+  __syncthreads();
+  if (threadIdx.x < 4) h_flags[threadIdx.x] = threadIdx.x == 2 ? flags[2] | bad : flags[threadIdx.x];
+}
+
 }  // namespace
+
+hipError_t rr_report(const double* w, const double* norms, int64_t b, const int* flags, double* h_w,
+                     double* h_norms, int* h_flags, hipStream_t st) {
+  k_rr_report<<<dim3(1), kThreads, 0, st>>>(w, norms, b, flags, h_w, h_norms, h_flags);
+  return hipGetLastError();
+}
 
 hipError_t rchfsi_init_f32(const double* R, int64_t ldr, int64_t n, int64_t b, double scale,
                            float* RY, float* RX, float* Ycopy, int64_t ld32, hipStream_t st) {
@@ -357,23 +392,15 @@ hipError_t copy_block(const double* in, int64_t ldi, double* out, int64_t ldo, i
   return hipGetLastError();
 }
 
-hipError_t scale_gram(const double* G, int64_t ldg, int64_t b, double* Gs, int64_t lds,
-                      double* s, int* bad_flag, hipStream_t st) {
-  k_gram_scale_vec<<<grid_for(b), kThreads, 0, st>>>(G, ldg, b, s, bad_flag);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  k_scale_sym<<<grid_for(b * b), kThreads, 0, st>>>(G, ldg, b, s, Gs, lds);
+hipError_t scale_gram(const double* G, int64_t ldg, int64_t b, bool lower, double* Gs, double* Gc,
+                      int64_t lds, double* s, int* bad_flag, hipStream_t st) {
+  k_scale_gram<<<grid_for(b * b), kThreads, 0, st>>>(G, ldg, b, lower, s, bad_flag, Gs, Gc, lds);
   return hipGetLastError();
 }
 
-hipError_t scale_sym(const double* G, int64_t ldg, int64_t b, const double* s, double* out,
-                     int64_t ldo, hipStream_t st) {
-  k_scale_sym<<<grid_for(b * b), kThreads, 0, st>>>(G, ldg, b, s, out, ldo);
-  return hipGetLastError();
-}
-
-hipError_t symmetrize(double* A, int64_t lda, int64_t b, hipStream_t st) {
-  k_symmetrize<<<grid_for(b * b), kThreads, 0, st>>>(A, lda, b);
+hipError_t scale_sym(const double* G, int64_t ldg, int64_t b, bool lower, const double* s,
+                     double* out, int64_t ldo, hipStream_t st) {
+  k_scale_sym<<<grid_for(b * b), kThreads, 0, st>>>(G, ldg, b, lower, s, out, ldo);
   return hipGetLastError();
 }
 
@@ -383,9 +410,9 @@ hipError_t symmetrize_panels(double* A, int64_t lda, int64_t b, int64_t w, hipSt
   return hipGetLastError();
 }
 
-hipError_t scale_columns(double* M, int64_t ldm, int64_t n, int64_t b, const double* v,
-                         hipStream_t st) {
-  k_scale_columns<<<grid_for(n * b), kThreads, 0, st>>>(M, ldm, n, b, v);
+hipError_t scale_columns(const double* M, int64_t ldm, double* out, int64_t ldo, int64_t n,
+                         int64_t b, const double* v, hipStream_t st) {
+  k_scale_columns<<<grid_for(n * b), kThreads, 0, st>>>(M, ldm, out, ldo, n, b, v);
   return hipGetLastError();
 }
 

@@ -1292,11 +1292,7 @@ chfsi_status finish_rr(chfsi_ctx* c, double* R, int64_t ldr, double* ritz, doubl
   const int64_t n = c->n, b = c->b;
   hipStream_t st = c->stream;
   CK(column_norms(R, ldr, n, b, c->norms, st));
-  CK(check_finite(c->w, b, c->dflags + 2, st));
-  CK(check_finite(c->norms, b, c->dflags + 2, st));
-  CK(hipMemcpyAsync(c->h_w, c->w, b * sizeof(double), hipMemcpyDeviceToHost, st));
-  CK(hipMemcpyAsync(c->h_norms, c->norms, b * sizeof(double), hipMemcpyDeviceToHost, st));
-  CK(hipMemcpyAsync(c->h_flags, c->dflags, 4 * sizeof(int), hipMemcpyDeviceToHost, st));
+  CK(rr_report(c->w, c->norms, b, c->dflags, c->h_w, c->h_norms, c->h_flags, st));
   CK(hipStreamSynchronize(st));
   if (c->h_flags[2] != 0) {
     set_error("non-finite Ritz value or residual norm");
@@ -1355,7 +1351,7 @@ chfsi_status rayleigh_ritz_svqb(chfsi_ctx* c, const double* Y, int64_t ldy, cons
   CK(hipMemcpyAsync(c->lamY, c->h_stage, k * sizeof(double), hipMemcpyHostToDevice, st));
   CK(hipEventRecord(c->ev_stage, st));
   CK(copy_block(c->E + first * b, b, c->T, b, b, k, st));
-  CK(scale_columns(c->T, b, b, k, c->lamY, st));
+  CK(scale_columns(c->T, b, c->T, b, b, k, c->lamY, st));
   CK(scale_rows(c->T, b, b, k, c->svec, st));
   {
     GemmDesc<double> g;   // Tmp (b x k) = Ga W
@@ -1385,7 +1381,6 @@ chfsi_status rayleigh_ritz_svqb(chfsi_ctx* c, const double* Y, int64_t ldy, cons
     h.ldc = b;
     CK(gemm<double>(h, st, c->ws));
   }
-  CK(symmetrize(c->Hp, b, k, st));
   CK(syev_traced(c->Hp, b, k, c->w, c->E, b, st, c->ws_eig, &sweeps, &c->jacobi_unconv,
                  c->h_flags + 8, c->ev_jac));
   if (c->jacobi_unconv) c->flags |= 2;
@@ -1458,8 +1453,7 @@ chfsi_status rotate_and_residual(chfsi_ctx* c, const double* Y, int64_t ldy, con
     return CHFSI_OK;
   }
   if ((s = rotate(c->AY, n, Tm, R, ldr, 1.0, nullptr)) != CHFSI_OK) return s;
-  CK(copy_block(Tm, b, c->TL, b, b, k, st));
-  CK(scale_columns(c->TL, b, b, k, c->w, st));
+  CK(scale_columns(Tm, b, c->TL, b, b, k, c->w, st));
   if ((s = rotate(BY, ldby, c->TL, R, ldr, -1.0, R)) != CHFSI_OK) return s;
   return CHFSI_OK;
 }
@@ -1483,7 +1477,7 @@ chfsi_status rayleigh_ritz(chfsi_ctx* c, const double* Y, int64_t ldy, double* X
     ldby = n;
   }
   // Gram matrices Ga = Y^T A Y, Gb = Y^T B Y (K = n).  Both are symmetric:
-  // only the tiles on and below the diagonal are formed, then mirrored.
+  // only the tiles on and below the diagonal are formed, and their lower triangle is read.
   auto gram = [&](const double* W, int64_t ldw, double* G) -> chfsi_status {
     GemmDesc<double> g;
     g.M = b;
@@ -1499,14 +1493,13 @@ chfsi_status rayleigh_ritz(chfsi_ctx* c, const double* Y, int64_t ldy, double* X
     g.ldc = b;
     g.lower_only = true;
     CK(gemm<double>(g, st, c->ws));
-    CK(symmetrize_panels(G, b, b, 1, st));
     return CHFSI_OK;
   };
   if ((s = gram(c->AY, n, c->Ga)) != CHFSI_OK) return s;
   if ((s = gram(BY, ldby, c->Gb)) != CHFSI_OK) return s;
   // column scaling s = diag(Gb)^{-1/2}; Cholesky of the scaled Gram matrix
-  CK(scale_gram(c->Gb, b, b, c->Gs, b, c->svec, c->dflags + 1, st));
-  CK(copy_block(c->Gs, b, c->Linv, b, b, b, st));      // kept for the SVQB fallback
+  // (Linv: kept for the SVQB fallback)
+  CK(scale_gram(c->Gb, b, b, true, c->Gs, c->Linv, b, c->svec, c->dflags + 1, st));
   CK(potrf_traced(c->Gs, b, c->Linv, c->dflags, st, c->ws, c->tri));
   CK(hipMemcpyAsync(c->h_flags, c->dflags, 4 * sizeof(int), hipMemcpyDeviceToHost, st));
   CK(hipStreamSynchronize(st));
@@ -1520,12 +1513,13 @@ chfsi_status rayleigh_ritz(chfsi_ctx* c, const double* Y, int64_t ldy, double* X
                 c->h_flags[0]);
       return CHFSI_ERR_NOT_SPD;
     }
+    CK(symmetrize_panels(c->Ga, b, b, 1, st));
     return rayleigh_ritz_svqb(c, Y, ldy, BY, ldby, X, ldx, R, ldr, ritz, resnorm);
   }
   // Linv = L^{-1}
   CK(cholqr_inverse(c->Gs, b, c->Linv, st, c->ws, c->tri));
   // Hp = Linv (s Ga s) Linv^T
-  CK(scale_sym(c->Ga, b, b, c->svec, c->Hp, b, st));
+  CK(scale_sym(c->Ga, b, b, true, c->svec, c->Hp, b, st));
   {
     GemmDesc<double> g;   // Tmp = Linv * Hp(scaled Ga)
     g.M = b;
@@ -1554,7 +1548,6 @@ chfsi_status rayleigh_ritz(chfsi_ctx* c, const double* Y, int64_t ldy, double* X
     h.ldc = b;
     CK(gemm<double>(h, st, c->ws));
   }
-  CK(symmetrize(c->Hp, b, b, st));
   int sweeps = 0;
   CK(syev_traced(c->Hp, b, b, c->w, c->E, b, st, c->ws_eig, &sweeps, &c->jacobi_unconv,
                  c->h_flags + 8, c->ev_jac));
@@ -1719,7 +1712,6 @@ chfsi_status rayleigh_ritz_complex_svqb(chfsi_ctx* c, const double* Y, int64_t l
     h.ldc = m;
     CK(gemm<double>(h, st, c->ws));
   }
-  CK(symmetrize(c->Hp, m, 2 * k, st));
   CK(syev_traced(c->Hp, m, 2 * k, c->w, c->E, m, st, c->ws_eig, &sweeps, &c->jacobi_unconv,
                  c->h_flags + 8, c->ev_jac));
   if (c->jacobi_unconv) c->flags |= 2;
@@ -1899,7 +1891,7 @@ chfsi_status rayleigh_ritz_complex(chfsi_ctx* c, const double* Y, int64_t ldy, d
     } else {
       if ((s = rotate(c->AYpl, c->Xt, c->Rpl, 1.0, nullptr)) != CHFSI_OK) return s;
       CK(copy_block(c->Xt, m, c->TL, m, m, m, st));
-      CK(scale_columns(c->TL, m, m, m, c->wdup, st));
+      CK(scale_columns(c->TL, m, c->TL, m, m, m, c->wdup, st));
       if ((s = rotate(BYpl, c->TL, c->Rpl, -1.0, c->Rpl)) != CHFSI_OK) return s;
     }
     // residual norms: r_j^2 = ||Re R_j||^2 + ||Im R_j||^2
@@ -1927,8 +1919,8 @@ chfsi_status rayleigh_ritz_complex(chfsi_ctx* c, const double* Y, int64_t ldy, d
     return CHFSI_OK;
   };
   // CholQR of the scaled embedded Gram matrix, projected matrix, Jacobi
-  CK(scale_gram(c->Gb, m, m, c->Gs, m, c->svec, c->dflags + 1, st));
-  CK(copy_block(c->Gs, m, c->Linv, m, m, m, st));      // kept for the SVQB fallback
+  // (Linv: kept for the SVQB fallback)
+  CK(scale_gram(c->Gb, m, m, false, c->Gs, c->Linv, m, c->svec, c->dflags + 1, st));
   CK(potrf_traced(c->Gs, m, c->Linv, c->dflags, st, c->ws, c->tri));
   CK(hipMemcpyAsync(c->h_flags, c->dflags, 4 * sizeof(int), hipMemcpyDeviceToHost, st));
   CK(hipStreamSynchronize(st));
@@ -1945,7 +1937,7 @@ chfsi_status rayleigh_ritz_complex(chfsi_ctx* c, const double* Y, int64_t ldy, d
     return rayleigh_ritz_complex_svqb(c, Y, ldy, X, ldx, R, ldr, ritz, resnorm, tail);
   }
   CK(cholqr_inverse(c->Gs, m, c->Linv, st, c->ws, c->tri));
-  CK(scale_sym(c->Ga, m, m, c->svec, c->Hp, m, st));
+  CK(scale_sym(c->Ga, m, m, false, c->svec, c->Hp, m, st));
   {
     GemmDesc<double> g;   // Tmp = Linv Hp
     g.M = m;
@@ -1974,7 +1966,6 @@ chfsi_status rayleigh_ritz_complex(chfsi_ctx* c, const double* Y, int64_t ldy, d
     h.ldc = m;
     CK(gemm<double>(h, st, c->ws));
   }
-  CK(symmetrize(c->Hp, m, m, st));
   int sweeps = 0;
   CK(syev_traced(c->Hp, m, m, c->w, c->E, m, st, c->ws_eig, &sweeps, &c->jacobi_unconv,
                  c->h_flags + 8, c->ev_jac));
@@ -2095,8 +2086,7 @@ chfsi_status rayleigh_ritz_slabs(chfsi_ctx* c, double* X, int64_t ldx, double* R
   chfsi_status s;
   CK(fill_zero(c->dflags, 4 * sizeof(int), st));
   if ((s = slab_grams(c, X, ldx)) != CHFSI_OK) return s;
-  CK(scale_gram(c->Gb, b, b, c->Gs, b, c->svec, c->dflags + 1, st));
-  CK(copy_block(c->Gs, b, c->Linv, b, b, b, st));
+  CK(scale_gram(c->Gb, b, b, false, c->Gs, c->Linv, b, c->svec, c->dflags + 1, st));
   CK(potrf_traced(c->Gs, b, c->Linv, c->dflags, st, c->ws, c->tri));
   CK(hipMemcpyAsync(c->h_flags, c->dflags, 4 * sizeof(int), hipMemcpyDeviceToHost, st));
   CK(hipStreamSynchronize(st));
@@ -2107,7 +2097,7 @@ chfsi_status rayleigh_ritz_slabs(chfsi_ctx* c, double* X, int64_t ldx, double* R
   int sweeps = 0;
   if (c->h_flags[0] == 0) {
     CK(cholqr_inverse(c->Gs, b, c->Linv, st, c->ws, c->tri));
-    CK(scale_sym(c->Ga, b, b, c->svec, c->Hp, b, st));
+    CK(scale_sym(c->Ga, b, b, false, c->svec, c->Hp, b, st));
     GemmDesc<double> g;
     g.M = b;
     g.N = b;
@@ -2134,7 +2124,6 @@ chfsi_status rayleigh_ritz_slabs(chfsi_ctx* c, double* X, int64_t ldx, double* R
     h.C = c->Hp;
     h.ldc = b;
     CK(gemm<double>(h, st, c->ws));
-    CK(symmetrize(c->Hp, b, b, st));
     CK(syev_traced(c->Hp, b, b, c->w, c->E, b, st, c->ws_eig, &sweeps, &c->jacobi_unconv,
                  c->h_flags + 8, c->ev_jac));
   if (c->jacobi_unconv) c->flags |= 2;
@@ -2187,7 +2176,7 @@ chfsi_status rayleigh_ritz_slabs(chfsi_ctx* c, double* X, int64_t ldx, double* R
   CK(hipMemcpyAsync(c->lamY, c->h_stage, k * sizeof(double), hipMemcpyHostToDevice, st));
   CK(hipEventRecord(c->ev_stage, st));
   CK(copy_block(c->E + first * b, b, c->T, b, b, k, st));
-  CK(scale_columns(c->T, b, b, k, c->lamY, st));
+  CK(scale_columns(c->T, b, c->T, b, b, k, c->lamY, st));
   CK(scale_rows(c->T, b, b, k, c->svec, st));
   {
     GemmDesc<double> g;
@@ -2217,7 +2206,6 @@ chfsi_status rayleigh_ritz_slabs(chfsi_ctx* c, double* X, int64_t ldx, double* R
     h.ldc = b;
     CK(gemm<double>(h, st, c->ws));
   }
-  CK(symmetrize(c->Hp, b, k, st));
   CK(syev_traced(c->Hp, b, k, c->w, c->E, b, st, c->ws_eig, &sweeps, &c->jacobi_unconv,
                  c->h_flags + 8, c->ev_jac));
   if (c->jacobi_unconv) c->flags |= 2;

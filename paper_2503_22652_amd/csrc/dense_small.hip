@@ -744,6 +744,19 @@ __device__ __forceinline__ f64x4_t rot_cols(const double* Z, const double (&yb)[
   return acc;
 }
 
+// the workgroup's largest of the threads' m (not NaN, not negative) into *out; every
+// thread of the workgroup takes part.  red: one entry a wave
+template <int THREADS>
+__device__ __forceinline__ void publish_max(double m, double* red, unsigned long long* out) {
+  for (int off = 32; off > 0; off >>= 1) m = fmax(m, __shfl_xor(m, off));
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < THREADS / 64; ++w) m = fmax(m, red[w]);
+    if (m > 0.0) atomicMax(out, static_cast<unsigned long long>(__double_as_longlong(m)));
+  }
+}
+
 union RoundSmem {
   struct {
     PairSmem ps;
@@ -759,12 +772,15 @@ union RoundSmem {
 // Workgroups [0, npairs) (when rcur >= 0): pair solves of round rcur on the
 // matrix after round rprev (rprev < 0: Pin itself).  The rest (when
 // rprev >= 0): round rprev's rotations as in k_jacobi_apply, Pin -> Pout (a
-// block both of whose factors are identities is copied), V in place.
+// block both of whose factors are identities is copied), V in place; offmax (given in a
+// sweep's last launch) collects the largest off-diagonal magnitude.
 __global__ __launch_bounds__(kPairThreads) void k_jacobi_round(
     const double* __restrict__ Pin, double* __restrict__ Pout, int64_t lda, double* V,
     int64_t ldv, int nblk, int npairs, int rprev, const double* Uprev, const int* skipprev,
-    int rcur, double* Ucur, int* skipcur, const double* scale, double tol, int* counter) {
+    int rcur, double* Ucur, int* skipcur, const double* scale, double tol, int* counter,
+    unsigned long long* offmax) {
   __shared__ RoundSmem sm;
+  __shared__ double red[kPairThreads / 64];
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int npw = rcur >= 0 ? npairs : 0;
   if (int(blockIdx.x) < npw) {
@@ -871,16 +887,20 @@ __global__ __launch_bounds__(kPairThreads) void k_jacobi_round(
   const bool sp = skipprev[P] != 0, sq = skipprev[Q] != 0;
   int IQ, JQ;
   block_pair(Q, rprev, nblk, &IQ, &JQ);
+  double mx = 0.0;
   if (sp && sq) {
     for (int idx = tid; idx < JP * JP; idx += kPairThreads) {
       const int i = idx % JP, j = idx / JP;
       const int64_t o1 = pair_index(i, IP, JPb) + int64_t(pair_index(j, IQ, JQ)) * lda;
-      Pout[o1] = Pin[o1];
+      const double v = Pin[o1];
+      Pout[o1] = v;
       if (P != Q) {
         const int64_t o2 = pair_index(i, IQ, JQ) + int64_t(pair_index(j, IP, JPb)) * lda;
         Pout[o2] = Pin[o2];
       }
+      if (P != Q || i != j) mx = fmax(mx, fabs(v));
     }
+    if (offmax) publish_max<kPairThreads>(mx, red, offmax);
     return;
   }
   for (int idx = tid; idx < JP * JP; idx += kPairThreads) {
@@ -900,35 +920,30 @@ __global__ __launch_bounds__(kPairThreads) void k_jacobi_round(
   __syncthreads();
   for (int idx = tid; idx < JP * JP; idx += kPairThreads) {
     const int i = idx % JP, j = idx / JP;
-    Pout[pair_index(i, IP, JPb) + int64_t(pair_index(j, IQ, JQ)) * lda] = m[i + j * LDJ];
-    if (P != Q)
-      Pout[pair_index(j, IQ, JQ) + int64_t(pair_index(i, IP, JPb)) * lda] = m[i + j * LDJ];
+    const double v = m[i + j * LDJ];
+    Pout[pair_index(i, IP, JPb) + int64_t(pair_index(j, IQ, JQ)) * lda] = v;
+    if (P != Q) Pout[pair_index(j, IQ, JQ) + int64_t(pair_index(i, IP, JPb)) * lda] = v;
+    if (P != Q || i != j) mx = fmax(mx, fabs(v));
   }
+  if (offmax) publish_max<kPairThreads>(mx, red, offmax);
 }
 
-// padded copy: P (bp x bp) = [A 0; 0 0]; V = I
+// padded copy of the symmetrised matrix, P (bp x bp) = [(A + A^T) / 2, 0; 0, 0], V = I,
+// and each workgroup's partial sum of squares
+constexpr int kFroParts = 256;
 __global__ __launch_bounds__(256) void k_jacobi_setup(const double* A, int64_t lda, int64_t b,
-                                                      double* P, double* V, int64_t bp) {
+                                                      double* P, double* V, int64_t bp,
+                                                      double* part) {
+  __shared__ double red[256];
   const int64_t total = bp * bp;
+  double s = 0.0;
   for (int64_t idx = blockIdx.x * int64_t(256) + threadIdx.x; idx < total;
        idx += int64_t(gridDim.x) * 256) {
-    const int64_t i = idx % bp, j = idx / bp;
-    P[idx] = (i < b && j < b) ? A[i + j * lda] : 0.0;
+    const int64_t j = idx / bp, i = idx - j * bp;
+    double v = 0.0;
+    if (i < b && j < b) v = i == j ? A[i + j * lda] : 0.5 * (A[i + j * lda] + A[j + i * lda]);
+    P[idx] = v;
     V[idx] = (i == j) ? 1.0 : 0.0;
-  }
-}
-
-// Frobenius norm of a b x b matrix: per-workgroup partial sums of squares
-// (k_fro_part, one column range each), then one workgroup adds the partials
-// in a fixed order (deterministic)
-constexpr int kFroParts = 64;
-__global__ __launch_bounds__(256) void k_fro_part(const double* A, int64_t lda, int64_t b,
-                                                  double* part) {
-  __shared__ double red[256];
-  double s = 0.0;
-  const int64_t c0 = b * blockIdx.x / kFroParts, c1 = b * (blockIdx.x + 1) / kFroParts;
-  for (int64_t idx = threadIdx.x; idx < (c1 - c0) * b; idx += 256) {
-    const double v = A[idx % b + (c0 + idx / b) * lda];
     s += v * v;
   }
   red[threadIdx.x] = s;
@@ -939,90 +954,69 @@ __global__ __launch_bounds__(256) void k_fro_part(const double* A, int64_t lda, 
   }
   if (threadIdx.x == 0) part[blockIdx.x] = red[0];
 }
-__global__ __launch_bounds__(64) void k_fro_final(const double* part, double* out) {
+
+// the Frobenius norm from the partial sums (in a fixed order), and the sweep's rotation
+// count and largest off-diagonal magnitude cleared
+__global__ __launch_bounds__(64) void k_jacobi_begin(const double* part, double* out, int* counter,
+                                                     unsigned long long* offmax) {
+  double s = 0.0;
+#pragma unroll
+  for (int i = 0; i < kFroParts / 64; ++i) s += part[threadIdx.x + 64 * i];
+  for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
   if (threadIdx.x == 0) {
-    double s = 0.0;
-    for (int i = 0; i < kFroParts; ++i) s += part[i];
     *out = sqrt(s) > 0 ? sqrt(s) : 1.0;
+    *counter = 0;
+    *offmax = 0;
   }
 }
 
-// largest off-diagonal magnitude of the bp x bp matrix: per-workgroup column
-// ranges (k_offmax_part), then out[0] = 1 if it is at most thresh_rel * scal[0]
-// (the Frobenius norm), else 0
-__global__ __launch_bounds__(256) void k_offmax_part(const double* P, int64_t bp, double* part) {
-  __shared__ double red[256];
-  double m = 0.0;
-  const int64_t c0 = bp * blockIdx.x / kFroParts, c1 = bp * (blockIdx.x + 1) / kFroParts;
-  for (int64_t idx = threadIdx.x; idx < (c1 - c0) * bp; idx += 256) {
-    const int64_t i = idx % bp, j = c0 + idx / bp;
-    if (i != j) m = fmax(m, fabs(P[i + j * bp]));
-  }
-  red[threadIdx.x] = m;
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if (threadIdx.x < w) red[threadIdx.x] = fmax(red[threadIdx.x], red[threadIdx.x + w]);
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) part[blockIdx.x] = red[0];
-}
-__global__ __launch_bounds__(64) void k_offmax_final(const double* part, const double* scal,
-                                                     double thresh_rel, int* done) {
+// a sweep's end: flags[0] = rotations, flags[1] = 1 if no off-diagonal magnitude is above
+// thresh_rel * scal[0] (the Frobenius norm); both sources cleared for the next sweep.
+// flags may be pinned host memory
+__global__ __launch_bounds__(64) void k_sweep_end(const double* scal, double thresh_rel,
+                                                  int* counter, unsigned long long* offmax,
+                                                  int* flags) {
   if (threadIdx.x == 0) {
-    double m = 0.0;
-    for (int i = 0; i < kFroParts; ++i) m = fmax(m, part[i]);
-    *done = (m <= thresh_rel * scal[0]) ? 1 : 0;
+    flags[0] = *counter;
+    flags[1] = __longlong_as_double(*offmax) <= thresh_rel * scal[0] ? 1 : 0;
+    *counter = 0;
+    *offmax = 0;
   }
 }
 
-// ascending sort of the diagonal (first b entries) by rank counting, then
-// gather eigenvector columns; the diagonal is staged through LDS in chunks
-__global__ __launch_bounds__(256) void k_jacobi_rank(const double* P, int64_t bp, int64_t b,
-                                                     double* w, int* perm) {
-  constexpr int kChunk = 1024;
-  __shared__ double dg[kChunk];
-  const int64_t i = blockIdx.x * int64_t(256) + threadIdx.x;
-  const double di = i < b ? P[i + i * bp] : 0.0;
-  int64_t rank = 0;
-  for (int64_t c0 = 0; c0 < b; c0 += kChunk) {
-    const int cn = int(b - c0 < kChunk ? b - c0 : kChunk);
-    __syncthreads();
-    for (int t = threadIdx.x; t < cn; t += 256) dg[t] = P[(c0 + t) + (c0 + t) * bp];
-    __syncthreads();
-    if (i < b) {
-      // eight independent counts, so that the LDS reads are not serialised
-      int cnt[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-      int t = 0;
-      for (; t + 8 <= cn; t += 8) {
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          const double dj = dg[t + u];
-          cnt[u] += (dj < di) || (dj == di && c0 + t + u < i);
-        }
-      }
-      for (; t < cn; ++t) {
-        const double dj = dg[t];
-        cnt[0] += (dj < di) || (dj == di && c0 + t < i);
-      }
-#pragma unroll
-      for (int u = 0; u < 8; ++u) rank += cnt[u];
-    }
-  }
-  if (i < b) {
-    w[rank] = di;
-    perm[rank] = int(i);
-  }
-}
-
-__global__ __launch_bounds__(256) void k_jacobi_gather(const double* V, int64_t bp, int64_t b,
-                                                       const int* perm, double* out,
-                                                       int64_t ldo) {
-  const int64_t total = b * b;
-  for (int64_t idx = blockIdx.x * int64_t(256) + threadIdx.x; idx < total;
+// largest off-diagonal magnitude of the bp x bp matrix into *offmax (the rounds without
+// the pipeline; else the last round's rotations collect it)
+__global__ __launch_bounds__(256) void k_offmax(const double* P, int64_t bp,
+                                                unsigned long long* offmax) {
+  __shared__ double red[4];
+  double m = 0.0;
+  for (int64_t idx = blockIdx.x * int64_t(256) + threadIdx.x; idx < bp * bp;
        idx += int64_t(gridDim.x) * 256) {
-    const int64_t i = idx % b, r = idx / b;
-    out[i + r * ldo] = V[i + int64_t(perm[r]) * bp];
+    const int64_t j = idx / bp, i = idx - j * bp;
+    if (i != j) m = fmax(m, fabs(P[idx]));
   }
+  publish_max<256>(m, red, offmax);
+}
+
+// ascending sort of the diagonal (first b entries) by rank counting: one workgroup per
+// entry finds its rank and moves its eigenvector column
+__global__ __launch_bounds__(256) void k_jacobi_sort(const double* P, const double* V, int64_t bp,
+                                                     int64_t b, double* w, double* out,
+                                                     int64_t ldo) {
+  __shared__ int cnt[4];
+  const int64_t j = blockIdx.x;
+  const double dj = P[j + j * bp];
+  int c = 0;
+  for (int64_t t = threadIdx.x; t < b; t += 256) {
+    const double dt = P[t + t * bp];
+    c += (dt < dj) || (dt == dj && t < j);
+  }
+  for (int off = 32; off > 0; off >>= 1) c += __shfl_xor(c, off);
+  if ((threadIdx.x & 63) == 0) cnt[threadIdx.x >> 6] = c;
+  __syncthreads();
+  const int64_t rank = cnt[0] + cnt[1] + cnt[2] + cnt[3];
+  if (threadIdx.x == 0) w[rank] = dj;
+  for (int64_t i = threadIdx.x; i < b; i += 256) out[i + rank * ldo] = V[i + j * bp];
 }
 
 inline int64_t grid_for(int64_t total) {
@@ -1161,7 +1155,7 @@ size_t syev_workspace_bytes(int64_t b) {
   const int64_t bp = jacobi_padded(b);
   const int64_t npairs = bp / JP;
   return size_t(3 * bp * bp + 2 * npairs * JP * JP + 16 + kFroParts) * sizeof(double) +
-         size_t(b + 64 + 2 * npairs) * sizeof(int);
+         size_t(64 + 2 * npairs) * sizeof(int);
 }
 
 // pipelined outer rounds (knob CHFSI_JACOBI_PIPE=0: a pair-solve launch and a
@@ -1183,15 +1177,13 @@ hipError_t syev_jacobi(double* A, int64_t lda, int64_t b, double* w, double* V, 
   double* P2 = Vp + bp * bp;                      // the pipelined rounds' second buffer
   double* U = P2 + bp * bp;                       // two sets of npairs JP x JP factors
   double* scal = U + 2 * int64_t(npairs) * JP * JP;   // [0]: Frobenius norm
-  int* counter = reinterpret_cast<int*>(scal + 16 + kFroParts);
-  int* perm = counter + 64;
-  int* skip = perm + b;                           // two sets of npairs flags
+  auto* offmax = reinterpret_cast<unsigned long long*>(scal + 1);
+  int* counter = reinterpret_cast<int*>(scal + 16 + kFroParts);   // [2], [3]: a sweep's flags
+  int* skip = counter + 64;                       // two sets of npairs flags
   hipError_t e;
-  k_jacobi_setup<<<grid_for(bp * bp), 256, 0, st>>>(A, lda, b, P, Vp, bp);
+  k_jacobi_setup<<<kFroParts, 256, 0, st>>>(A, lda, b, P, Vp, bp, scal + 16);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  k_fro_part<<<kFroParts, 256, 0, st>>>(A, lda, b, scal + 16);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  k_fro_final<<<1, 64, 0, st>>>(scal + 16, scal);
+  k_jacobi_begin<<<1, 64, 0, st>>>(scal + 16, scal, counter, offmax);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   const double tol = 1e-15;
   // sweep cap (knob CHFSI_JACOBI_MAX_SWEEPS, for tests of the cap's report)
@@ -1214,7 +1206,7 @@ hipError_t syev_jacobi(double* A, int64_t lda, int64_t b, double* w, double* V, 
                      0, st>>>(
         P, P2, bp, Vp, bp, nblk, npairs, rotate ? r - 1 : -1, rotate ? U + pu * usz : nullptr,
         rotate ? skip + pu * npairs : nullptr, solve ? r : -1, solve ? U + cu * usz : nullptr,
-        solve ? skip + cu * npairs : nullptr, scal, tol, counter);
+        solve ? skip + cu * npairs : nullptr, scal, tol, counter, r == R ? offmax : nullptr);
     const hipError_t le = hipGetLastError();
     if (le == hipSuccess && rotate) std::swap(P, P2);
     return le;
@@ -1228,7 +1220,6 @@ hipError_t syev_jacobi(double* A, int64_t lda, int64_t b, double* w, double* V, 
   const bool early = pipe && pinned_flags && ev && R >= 2;
   int started = 0;   // launches of the current sweep already queued
   for (; sweeps < max_outer; ++sweeps) {
-    if (started == 0 && (e = fill_zero(counter, sizeof(int), st)) != hipSuccess) return e;
     if (pipe) {
       for (int r = started; r <= R; ++r)
         if ((e = launch(r)) != hipSuccess) return e;
@@ -1245,16 +1236,12 @@ hipError_t syev_jacobi(double* A, int64_t lda, int64_t b, double* w, double* V, 
     }
     // converged when the sweep rotated nothing, or when no off-diagonal entry
     // is left above the threshold (every pair of a further sweep would skip)
-    k_offmax_part<<<kFroParts, 256, 0, st>>>(P, bp, scal + 16);
-    k_offmax_final<<<1, 64, 0, st>>>(scal + 16, scal, tol, counter + 1);
+    if (!pipe) k_offmax<<<grid_for(bp * bp), 256, 0, st>>>(P, bp, offmax);
+    k_sweep_end<<<1, 64, 0, st>>>(scal, tol, counter, offmax, early ? pinned_flags : counter + 2);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (early) {
-      if ((e = hipMemcpyAsync(pinned_flags, counter, 2 * sizeof(int), hipMemcpyDeviceToHost,
-                              st)) != hipSuccess)
-        return e;
       if ((e = hipEventRecord(ev, st)) != hipSuccess) return e;
       if (sweeps + 1 < max_outer) {
-        if ((e = fill_zero(counter, sizeof(int), st)) != hipSuccess) return e;
         for (int r = 0; r < 2; ++r)
           if ((e = launch(r)) != hipSuccess) return e;
         started = 2;
@@ -1271,7 +1258,7 @@ hipError_t syev_jacobi(double* A, int64_t lda, int64_t b, double* w, double* V, 
       continue;
     }
     int host_flags[2] = {0, 0};
-    if ((e = hipMemcpyAsync(host_flags, counter, 2 * sizeof(int), hipMemcpyDeviceToHost, st)) !=
+    if ((e = hipMemcpyAsync(host_flags, counter + 2, 2 * sizeof(int), hipMemcpyDeviceToHost, st)) !=
         hipSuccess)
       return e;
     if ((e = hipStreamSynchronize(st)) != hipSuccess) return e;
@@ -1282,9 +1269,7 @@ hipError_t syev_jacobi(double* A, int64_t lda, int64_t b, double* w, double* V, 
       break;
     }
   }
-  k_jacobi_rank<<<dim3(unsigned((b + 255) / 256)), 256, 0, st>>>(P, bp, b, w, perm);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  k_jacobi_gather<<<grid_for(b * b), 256, 0, st>>>(Vp, bp, b, perm, V, ldv);
+  k_jacobi_sort<<<dim3(unsigned(b)), 256, 0, st>>>(P, Vp, bp, b, w, V, ldv);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if (sweeps_out) *sweeps_out = sweeps;
   // the tolerance was not met within the cap

@@ -298,18 +298,21 @@ hipError_t convert_f64_f32(const double* in, int64_t ldi, float* out, int64_t ld
 hipError_t copy_block(const double* in, int64_t ldi, double* out, int64_t ldo, int64_t n,
                       int64_t b, hipStream_t st);
 // B <- diag(s) A diag(s) with s = 1/sqrt(diag(G)); writes s
-hipError_t scale_gram(const double* G, int64_t ldg, int64_t b, double* Gs, int64_t lds,
-                      double* s, int* bad_flag, hipStream_t st);
-hipError_t scale_sym(const double* G, int64_t ldg, int64_t b, const double* s, double* out,
-                     int64_t ldo, hipStream_t st);
-// out = 0.5 (A + A^T) in place on a b x b matrix
-hipError_t symmetrize(double* A, int64_t lda, int64_t b, hipStream_t st);
+// (Gc: a second copy of Gs; lower: only G's lower triangle holds it)
+hipError_t scale_gram(const double* G, int64_t ldg, int64_t b, bool lower, double* Gs, double* Gc,
+                      int64_t lds, double* s, int* bad_flag, hipStream_t st);
+hipError_t scale_sym(const double* G, int64_t ldg, int64_t b, bool lower, const double* s,
+                     double* out, int64_t ldo, hipStream_t st);
+// w, norms (b each) and the four flags to pinned host memory; h_flags[2] is also set
+// by a non-finite value
+hipError_t rr_report(const double* w, const double* norms, int64_t b, const int* flags, double* h_w,
+                     double* h_norms, int* h_flags, hipStream_t st);
 // completes a symmetric matrix of which the lower block panels of width w were
 // formed (w = 1: copies the strictly lower part to the upper part)
 hipError_t symmetrize_panels(double* A, int64_t lda, int64_t b, int64_t w, hipStream_t st);
 // columns of M scaled by v: M[:,j] *= v[j]
-hipError_t scale_columns(double* M, int64_t ldm, int64_t n, int64_t b, const double* v,
-                         hipStream_t st);
+hipError_t scale_columns(const double* M, int64_t ldm, double* out, int64_t ldo, int64_t n,
+                         int64_t b, const double* v, hipStream_t st);
 // rows of M scaled by v: M[i,:] *= v[i]
 hipError_t scale_rows(double* M, int64_t ldm, int64_t n, int64_t b, const double* v,
                       hipStream_t st);
@@ -342,7 +345,7 @@ hipError_t potrf_inverse(double* A, int64_t lda, int64_t b, int* info, double* L
 // inverses of this L (left by potrf_lower)
 hipError_t trsm_lower_left(const double* L, int64_t ldl, double* X, int64_t ldx, int64_t b,
                            int64_t nrhs, hipStream_t st, const Workspace& ws, double* tri);
-// Symmetric eigensolver (parallel block Jacobi).  A (b x b) is destroyed.
+// Symmetric eigensolver (parallel block Jacobi) of (A + A^T) / 2, A b x b.
 // w: ascending eigenvalues (device, b); V: eigenvectors (device, b x b, ldv).
 // scratch from ws; sweeps reported through *sweeps_out (host) if non-null;
 // *unconverged_out (host, if non-null) = 1 when the sweep cap was reached with
