@@ -68,7 +68,8 @@ struct KernelArgsCommon {
   int64_t bsA, bsB, bsC, bsC1;
   int vecA, vecB;           // 16-byte vector loads allowed along the contiguous dim
   int tiles_m, tiles_n;
-  int lower;                // skip tiles strictly above the diagonal
+  int lower;                // only the tiles that reach the diagonal or below
+  int tiles;                // tiles in all (per batch entry and split)
 };
 
 template <typename T>
@@ -88,6 +89,13 @@ __device__ __forceinline__ int xcd_remap(int h, int G) {
   const int xcd = h & 7, slot = h >> 3;
   const int full = G >> 3, rem = G & 7;
   return (xcd < rem) ? xcd * (full + 1) + slot : rem * (full + 1) + (xcd - rem) * full + slot;
+}
+
+// tiles of tile row m_tile that reach the diagonal or below
+template <int BM, int BN>
+__host__ __device__ __forceinline__ int lower_tiles(int m_tile, int tiles_n) {
+  const int64_t w = (int64_t(m_tile + 1) * BM + BN - 1) / BN;
+  return w < tiles_n ? int(w) : tiles_n;
 }
 
 template <typename T>
@@ -217,10 +225,14 @@ __global__ __launch_bounds__(256, MINW) void gemm_kernel(KernelArgs<T> args) {
   const KernelArgsCommon& c = args.c;
   const int G = gridDim.x;
   const int t = xcd_remap(blockIdx.x, G);
-  const int tiles_mn = c.tiles_m * c.tiles_n;
-  const int n_tile = t % c.tiles_n;
-  const int m_tile = (t / c.tiles_n) % c.tiles_m;
-  const int zs = t / tiles_mn;                  // batch * splits + split
+  const int zs = t / c.tiles;                   // batch * splits + split
+  int n_tile = t - zs * c.tiles, m_tile = 0;
+  if (c.lower) {
+    for (int w; n_tile >= (w = lower_tiles<BM, BN>(m_tile, c.tiles_n)); ++m_tile) n_tile -= w;
+  } else {
+    m_tile = n_tile / c.tiles_n;
+    n_tile -= m_tile * c.tiles_n;
+  }
   const int split = zs % c.splits;
   const int bz = zs / c.splits;
 
@@ -229,7 +241,6 @@ __global__ __launch_bounds__(256, MINW) void gemm_kernel(KernelArgs<T> args) {
   const T* __restrict__ ks = args.kscale;
   const int64_t m0 = int64_t(m_tile) * BM;
   const int64_t n0 = int64_t(n_tile) * BN;
-  if (c.lower && n0 >= m0 + BM) return;        // whole tile above the diagonal
   const int64_t kbeg = int64_t(split) * c.kchunk;
   const int64_t kend = std::min<int64_t>(c.K, kbeg + c.kchunk);
   const int nk = kend > kbeg ? int((kend - kbeg + BK - 1) / BK) : 0;
@@ -639,9 +650,12 @@ static constexpr int kNumCU = 256;
 // 64x64 / 8 402 ms, 128x128 / 8 403 ms; 4 splits 456-593 ms; 16-64 splits
 // 610-990 ms (a k-range per XCD no longer holds).  Up to 640 columns that is too
 // few workgroups (72 on or below the diagonal at 300), and the panels of several
-// k-ranges fit an L2: 64 x 64 tiles, which waste less on the diagonal, and splits
-// up to 64.  Whole Rayleigh-Ritz, us, 128x64 / 8 and 64x64 / 64: 64^3 x 300 11245 and
-// 7329, 64^3 x 600 24926 and 18689, 40^3 x 200 4206 and 3193.  Tuning knobs (read
+// k-ranges fit an L2: 64 x 64 tiles, which waste less on the diagonal, and as many
+// splits (up to 64) as share the tiles most evenly over the CUs.  Whole Rayleigh-Ritz,
+// us, 128x64 / 8 and 64x64 / 64: 64^3 x 300 11245 and 7329, 64^3 x 600 24926 and 18689,
+// 40^3 x 200 4206 and 3193.  A 64^3 x 300 product, 64 and 51 splits: 915 and 669 (960
+// workgroups do not fit the chip's 768 places at once, 765 do; before, the tiles above
+// the diagonal were launched too and left at once, which upset the balance).  Tuning knobs (read
 // per call): CHFSI_GEMM64_LONG_CFG (0 = 128x128, 1 = 128x64, 2 = 64x64) and
 // CHFSI_GEMM64_LONG_SPLITS (power of two, at most 64).
 static int env_int(const char* name, int dflt) {
@@ -661,11 +675,23 @@ static void plan_impl(int64_t M, int64_t N, int64_t K, int batch, int* config, i
     if (lcfg < 0 || lcfg >= kNumF64) lcfg = 1;
     const Cfg& w = kCfgF64[lcfg];
     const int64_t max_s = std::max<int64_t>(1, K / (8 * w.BK));
-    // narrow: about 2048 workgroups on and below the diagonal
-    const int64_t t = (std::max(M, N) + 63) / 64, low = t * (t + 1) / 2;
-    const int lsplits = env_int("CHFSI_GEMM64_LONG_SPLITS", wide ? 8 : int(2048 / low));
     int s = 1;
-    while (s * 2 <= lsplits && s * 2 <= max_s && s < 64) s *= 2;
+    const int lsplits = env_int("CHFSI_GEMM64_LONG_SPLITS", wide ? 8 : 0);
+    if (lsplits > 0) {
+      while (s * 2 <= lsplits && s * 2 <= max_s && s < 64) s *= 2;
+    } else {
+      // narrow: the splits that leave the busiest CU the least work, tiles on and below
+      // the diagonal over 256 CUs
+      const int64_t t = (std::max(M, N) + 63) / 64, low = t * (t + 1) / 2 * batch;
+      double best = 0.0;
+      for (int64_t q = std::min<int64_t>(64, max_s); q >= 1; --q) {
+        const double work = double((low * q + kNumCU - 1) / kNumCU) / double(q);
+        if (best == 0.0 || work < 0.97 * best) {
+          best = work;
+          s = int(q);
+        }
+      }
+    }
     *config = lcfg;
     *splits = s;
     return;
@@ -769,7 +795,14 @@ static hipError_t launch_cfg(const GemmDesc<T>& d, hipStream_t st, const Workspa
       a.partial = static_cast<T*>(ws.ptr);
     }
   }
-  const int64_t grid = int64_t(c.tiles_m) * c.tiles_n * c.splits * d.batch;
+  int64_t tiles = int64_t(c.tiles_m) * c.tiles_n;
+  if (c.lower) {
+    tiles = 0;
+    for (int i = 0; i < c.tiles_m; ++i) tiles += lower_tiles<BM, BN>(i, c.tiles_n);
+  }
+  if (tiles > 0x7fffffff) return hipErrorInvalidValue;
+  c.tiles = int(tiles);
+  const int64_t grid = tiles * c.splits * d.batch;
   if (grid <= 0) return hipSuccess;
   if (grid > 0x7fffffff) return hipErrorInvalidValue;
   if (d.ev_begin) {
