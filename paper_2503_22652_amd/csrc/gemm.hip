@@ -703,30 +703,54 @@ static void plan_impl(int64_t M, int64_t N, int64_t K, int batch, int* config, i
     const int bc = env_int("CHFSI_GEMM64_BIG_CFG", kGeneral);
     if (bc >= 0 && bc < kNumF64) gcfg = bc;
   }
-  // (splits by the 64-wide tiling whatever the column tile: the partials' size and
-  // the order of summation do not depend on it)
-  const Cfg& f = kCfgF64[gcfg];
-  const int64_t tiles = ((M + f.BM - 1) / f.BM) * ((N + f.BN - 1) / f.BN) * batch;
-  const int64_t target = int64_t(kNumCU) * 8;
-  const int64_t max_s = std::max<int64_t>(1, K / (8 * f.BK));
-  int s = 1;
-  while (tiles * s < target && s * 2 <= max_s && s < 64) s *= 2;
-  // The column tile: the least work, padding included, at each one's rate relative
-  // to the 64-wide one's; where that leaves the chip half empty, the 32-wide one.
-  // Measured (plain filter of degree 16, us, tiles of 64 / 32 / 16): N = 3001, 16
-  // columns 508 / 361 / 347, 48 562 / 608 / 614, 77 965 / 820 / 900, 96 1007 / 850 /
-  // 1043, 128 1040 / 1074 / 1321; 6000 x 160 4268 / 4010 / 5470, 320 7010 / 7618 /
-  // 10212; 700 x 48 249 / 209 / 216.  (Tiles of 48 and 80 were no better at any of these.)
+  // Column tile and k-splits: the least of a model of the step's time in us.  A
+  // workgroup takes K / s k values and about 64 more for its start and end, the busiest
+  // CU has ceil(tiles s / 256) of them, one to three on a CU do not hide their latency,
+  // and splits cost a launch and the partials' way to memory and back.  The largest s
+  // within 1.5% of it, for evenness.  Unit times (a k value of a 64 x {64, 32, 16} tile)
+  // and the factors are fitted to the plain filter of degree 16, us at s = 1, 2, 4, 5, 7,
+  // 8, 16: 3001 x 77 (32-wide) 1646 1208 910 776 735 815 816; 3001 x 128 2229 1186 1087
+  // 930 968 901 1034; 700 x 48 450 296 221 208 209 183 218 and 180 at 10; 6000 x 320 7322
+  // 7286 7103 7169 6985 6979 7898; tiles of 64 / 32 / 16: 3001 x 16 508 / 361 / 347, 48
+  // 562 / 608 / 614, 77 965 / 820 / 900, 6000 x 160 4268 / 4010 / 5470, 320 7010 / 7618.
+  // (Tiles of 48 and 80 were no better at any of these.)  Before, s was a power of two
+  // for 8 workgroups a CU: 3001 x 77 816, 3001 x 128 1087, 700 x 48 221, 1024 x 80 283.
+  struct Tile {
+    int cfg, width;
+    double unit;
+  };
+  static const Tile kTiles[] = {{kGeneral, 64, 0.036}, {4, 32, 0.019}, {3, 16, 0.015}};
+  const int64_t max_s = std::max<int64_t>(1, std::min<int64_t>(64, K / 64));
+  auto cost = [&](const Tile& t, int64_t s) {
+    const int64_t tiles = (M + 63) / 64 * ((N + t.width - 1) / t.width) * batch;
+    const int64_t per = (tiles * s + kNumCU - 1) / kNumCU;
+    static const double kFew[] = {1.0, 1.3, 1.12, 1.04};
+    const double few = per > 3 ? 1.0 : (t.width == 16 && per == 1 ? 1.5 : kFew[per]);
+    double c = t.unit * double(per) * (double(K) / double(s) + 64.0) * few;
+    if (s > 1) c += 4.0 + double(s) * double(M) * double(N) * batch * 1.6e-6;
+    return c;
+  };
+  const Tile* tile = &kTiles[0];
+  int64_t s = 1;
   if (gcfg == kGeneral) {
-    auto cost = [N](int w, double rate) { return double((N + w - 1) / w * w) / rate; };
-    const double c64 = cost(64, 1.0), c32 = cost(32, 0.95), c16 = cost(16, 0.6);
-    if (c16 < std::min(c32, c64))
-      gcfg = 3;
-    else if (c32 < c64 || tiles * s < 2 * kNumCU)
-      gcfg = 4;
+    double best = cost(*tile, 1);
+    for (const Tile& t : kTiles)
+      for (int64_t q = 1; q <= max_s; ++q)
+        if (const double c = cost(t, q); c < best) {
+          best = c;
+          tile = &t;
+          s = q;
+        }
+    gcfg = tile->cfg;
+    for (int64_t q = max_s; q > s; --q)
+      if (cost(*tile, q) < 1.015 * best) s = q;
+  } else {
+    const Cfg& f = kCfgF64[gcfg];
+    const int64_t tiles = ((M + f.BM - 1) / f.BM) * ((N + f.BN - 1) / f.BN) * batch;
+    while (tiles * s < int64_t(kNumCU) * 8 && s * 2 <= K / (8 * f.BK) && s < 64) s *= 2;
   }
   *config = gcfg;
-  *splits = s;
+  *splits = int(s);
 }
 
 template <typename T>
@@ -862,6 +886,9 @@ hipError_t gemm(const GemmDesc<T>& d, hipStream_t st, const Workspace& ws, int f
   int cfg, splits;
   plan_impl<T>(d.M, d.N, d.K, d.batch, &cfg, &splits);
   if (force_config >= 0 && force_config < kNumF64) cfg = force_config;
+  // (no more splits than the scratch holds)
+  splits = int(std::max<size_t>(1, std::min<size_t>(size_t(splits), ws.ptr ? ws.bytes /
+               (size_t(d.M) * size_t(d.N) * size_t(std::max(d.batch, 1)) * sizeof(T)) : 1)));
   if (force_splits > 0) splits = force_splits;
   if (d.K <= 0) splits = 1;
   hipError_t gerr = hipSuccess;

@@ -63,6 +63,13 @@ def test_fp64_filter_product_edges(method, pad, n, b):
     assert_columns(Y.cpu().numpy(), ref, np.linalg.norm(ref, axis=0), "fp64", 4, n, f"n {n} b {b}")
 
 
+@pytest.mark.parametrize("n,b", [(700, 48), (1003, 81), (1601, 144), (1300, 16)])
+def test_fp64_product_odd_splits(n, b):
+    """Sizes whose plans take split counts that are no powers of two, with a short last
+    k range."""
+    test_fp64_filter_product_edges(P.METHOD_RCHFSI, 3, n, b)
+
+
 @pytest.mark.parametrize("n,b", [(2065, 129), (2305, 130), (4111, 191)])
 def test_fp64_gram_many_splits(n, b):
     """Blocks of 128 <= b <= 640 with n >= 16 b: odd k ranges over up to 64 splits."""
