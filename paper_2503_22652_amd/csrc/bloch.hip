@@ -185,17 +185,17 @@ __device__ __forceinline__ void boundary_point(int t, int nx, int ny, int nz, in
   *x = (r & 1) ? nx - 1 : 0;
 }
 
-// Pairs of columns per thread of the correction kernels: the geometry, wrap
-// phase and weight of each wrapped offset are computed once and applied to
-// kPairs column pairs (independent gathers).
-constexpr int kPairs = 16;
+// kPairs: pairs of columns per thread of the correction kernels.  The geometry, wrap
+// phase and weight of each wrapped offset are computed once and applied to kPairs column
+// pairs (independent gathers), so the most that leave a workgroup to each CU
+// (correction_pairs).
 
 // The correction at boundary point t for column pairs (j, b + j), j in
 // [j0, j0 + kPairs) (those below b): out(j) = alpha * sum over the wrapped
 // offsets o of w(p, o) (phi(o) - 1) (dinv .* src)(p + o), accumulated in C.
 // RMW: dst(p) += out (planar block, ld ldd); else corr(t) = out (ld ldd).
 // colscale (RMW only; may be null): out(j) is multiplied by colscale[j].
-template <typename T, typename C, bool RMW>
+template <typename T, typename C, bool RMW, int kPairs>
 __global__ __launch_bounds__(kThreads) void k_bloch(FixArgs a, const double* __restrict__ V,
                                                     const double* __restrict__ dinv, double alpha,
                                                     const double* __restrict__ colscale,
@@ -408,18 +408,49 @@ hipError_t bloch_from_planar(const double* P, int64_t n, int64_t b, double* Z, i
   return hipGetLastError();
 }
 
+// Column pairs per thread: the most of 16, 8, 4 and 2 that still gives 256 workgroups.
+// Whole filters, us, 16 / 8 / 4 / 2: 64^3 x 48 BF16 2974 (282 workgroups) / 3105 / 3056 /
+// 3237, 100^3 x 64 7696 / 7810 / 7993 / 8460; 24 x 20 x 28, 6 columns 689 / 691 / 553 /
+// 475 (21 workgroups at 2), 40 x 64 x 33 x 20 FP32 927 / 962 / 872 / 812, 48^3 x 30 FP64
+// 1673 / 1589 / 1494 / 1527.
+static int correction_pairs(int64_t nb, int64_t pairs) {
+  const int64_t blocks = (nb + kThreads - 1) / kThreads;
+  int p = 16;
+  while (p > 2 && blocks * ((pairs + p - 1) / p) < 256) p /= 2;
+  return p;
+}
+
+template <typename T, typename C, bool RMW>
+static hipError_t launch_correction(const chfsi_operator& op, const double* dinv, double alpha,
+                                    const double* colscale, const T* src, int64_t lds, const T* edge,
+                                    void* dst, int64_t ldd, int64_t pairs, int64_t nb,
+                                    hipStream_t st) {
+  const FixArgs fa = fix_args(op);
+  const int p = correction_pairs(nb, pairs);
+  const dim3 grid(unsigned((nb + kThreads - 1) / kThreads * ((pairs + p - 1) / p)));
+  auto go = [&](auto* kernel) {
+    kernel<<<grid, kThreads, 0, st>>>(fa, op.field, dinv, alpha, colscale, src, lds, edge, dst, ldd,
+                                      pairs, int(nb));
+    return hipGetLastError();
+  };
+  switch (p) {
+    case 16: return go(k_bloch<T, C, RMW, 16>);
+    case 8: return go(k_bloch<T, C, RMW, 8>);
+    case 4: return go(k_bloch<T, C, RMW, 4>);
+    default: return go(k_bloch<T, C, RMW, 2>);
+  }
+}
+
 template <typename F>
 hipError_t bloch_fix(const chfsi_operator& op, const double* dinv, double alpha, const F* src,
                      int64_t lds, F* dst, int64_t ldd, int64_t pairs, hipStream_t st,
                      const double* colscale, const F* edge) {
   if (!fix_ok(op, pairs) || lds < op.n || ldd < op.n) return hipErrorInvalidValue;
   const int64_t nb = bloch_boundary_points(op.nx, op.ny, op.nz);
-  const dim3 grid(unsigned((nb + kThreads - 1) / kThreads * ((pairs + kPairs - 1) / kPairs)));
   // the correction accumulates in FP64 for FP64 blocks, else FP32
   using C = typename std::conditional<sizeof(F) == 8, double, float>::type;
-  k_bloch<F, C, true><<<grid, kThreads, 0, st>>>(fix_args(op), op.field, dinv, alpha, colscale,
-                                                 src, lds, edge, dst, ldd, pairs, int(nb));
-  return hipGetLastError();
+  return launch_correction<F, C, true>(op, dinv, alpha, colscale, src, lds, edge, dst, ldd, pairs,
+                                       nb, st);
 }
 
 template <typename T, typename C>
@@ -428,10 +459,8 @@ hipError_t bloch_corr(const chfsi_operator& op, const double* dinv, double alpha
                       hipStream_t st) {
   const int64_t nb = bloch_boundary_points(op.nx, op.ny, op.nz);
   if (!fix_ok(op, pairs) || lds < op.n || ldc < nb) return hipErrorInvalidValue;
-  const dim3 grid(unsigned((nb + kThreads - 1) / kThreads * ((pairs + kPairs - 1) / kPairs)));
-  k_bloch<T, C, false><<<grid, kThreads, 0, st>>>(fix_args(op), op.field, dinv, alpha, nullptr,
-                                                  src, lds, edge, corr, ldc, pairs, int(nb));
-  return hipGetLastError();
+  return launch_correction<T, C, false>(op, dinv, alpha, nullptr, src, lds, edge, corr, ldc, pairs,
+                                        nb, st);
 }
 
 template hipError_t bloch_init<double>(const double*, int64_t, int64_t, int64_t, double, double*,
