@@ -30,17 +30,18 @@ PEAK_FP32_MFMA_TFLOPS = 157.3
 PEAK_FP64_MFMA_TFLOPS = 78.6
 PEAK_BF16_MFMA_TFLOPS = 2500.0
 PEAK_HBM_GBS = 8000.0
-# HBM bytes per FP32 filter step at N = 8192, b = 320: the GEMM (64x64x32
-# tiles, split-K 8) plus the split-K reduction that carries the three-term
+# the dense FP32 step runs as six bfloat16 products of exact three-part splits
+PEAK_FP32_SPLIT_TFLOPS = PEAK_BF16_MFMA_TFLOPS / 6
+# HBM bytes per FP32 filter step at N = 8192, b = 320: the product (128x160
+# tiles, split-K 4) plus the split-K reduction that carries the three-term
 # epilogue, the two kernels the step's timing brackets.  FETCH_SIZE and
 # WRITE_SIZE from two rocprofv3 counter passes over this script, scaled by what
 # the same counters read for a 1 GiB device copy (FETCH x 2.000, WRITE x 1.000);
 # summary under profiles/.  Other shapes report null.
-TRAFFIC_F32_FILTER_STEP = {(8192, 320): 511.5e6}
+TRAFFIC_F32_FILTER_STEP = {(8192, 320): 492.3e6}
 # the same for the BF16-product step (product, split-K reduction that also
-# rounds the next step's operand; the rounding pass of a filter's first step
-# averaged over its 19 steps: profiles/dense_n8192_b320_bf16_wide_step_traffic.md)
-TRAFFIC_BF16_FILTER_STEP = {(8192, 320): 277.2e6}
+# packs the next step's operand: profiles/dense_n8192_b320_split_step.md)
+TRAFFIC_BF16_FILTER_STEP = {(8192, 320): 276.0e6}
 # the same for the BF16 z-march filter step on the 128^3 grid (block 1200) and
 # the 160^3 grid (block 2400)
 TRAFFIC_ZMARCH = {(128, 1200, "bf16"): 21.98e9, (160, 2400, "bf16"): 89.61e9}
@@ -263,7 +264,7 @@ def main():
     # timed steps: FP32 R-ChFSI outer iterations (filter + RR + residuals)
     # ------------------------------------------------------------------
     dprec = P.PREC_BF16 if args.dense_prec == "bf16" else P.PREC_FP32
-    peak = PEAK_BF16_MFMA_TFLOPS if args.dense_prec == "bf16" else PEAK_FP32_MFMA_TFLOPS
+    peak = PEAK_BF16_MFMA_TFLOPS if args.dense_prec == "bf16" else PEAK_FP32_SPLIT_TFLOPS
     ctx = ctx_for(P.METHOD_RCHFSI, dprec, profile=1)
     # lambda_max for the explicit filter calls: the library's Lanczos estimate
     torch.cuda.synchronize()
@@ -339,17 +340,17 @@ def main():
         "roofline": {
             "bound": "mfma",
             "achieved": round(achieved_tflops, 2),
-            "peak": peak,
+            "peak": round(peak, 1),
             "unit": "TFLOP/s",
             "frac": round(achieved_tflops / peak, 4),
             "traffic": (TRAFFIC_F32_FILTER_STEP if args.dense_prec == "fp32"
                         else TRAFFIC_BF16_FILTER_STEP).get((n, b)),
             "traffic_unit": "bytes per launch",
-            "kernel": ("gemm_kernel<float> + splitk_reduce4_kernel (FP32 residual-filter step, "
-                       "2*N^2*b flops per launch)") if args.dense_prec == "fp32" else
-                      ("gemm_bf16_wide_kernel + splitk_reduce4_kernel, which also rounds the "
-                       "next step's operand (k_scale_bf16 on a filter's first step) (BF16-product "
-                       "residual-filter step, 2*N^2*b flops per launch)"),
+            "kernel": ("k_step_large<5,3,1> + k_step_reduce<3> (FP32 residual-filter step as six "
+                       "bfloat16 products, 2*N^2*b flops per launch; peak: bf16 MFMA / 6)")
+                      if args.dense_prec == "fp32" else
+                      ("k_step_large<5,1,2> + k_step_reduce<1>, which also packs the next step's "
+                       "operand (BF16-product residual-filter step, 2*N^2*b flops per launch)"),
             "ms_per_launch": round(per_launch_ms, 4),
         },
     }
