@@ -754,8 +754,8 @@ chfsi_status filter_rchfsi(chfsi_ctx* c, const double* X, int64_t ldx, const dou
   double fl = 0.0;
   const bool dense = c->A.kind == CHFSI_OP_DENSE, csr = c->A.kind == CHFSI_OP_CSR;
   if (c->prm.filter_prec == CHFSI_PREC_FP32 || (c->prm.filter_prec == CHFSI_PREC_BF16 && dense)) {
-    // FP32 filter blocks; the operator product is FP32 MFMA, or BF16 MFMA on
-    // the bfloat16 copy of A (dense BF16)
+    // FP32 filter blocks; a dense operator's product is bfloat16 MFMA, on exact three-way
+    // splits (FP32) or on the bfloat16 copy of A (dense BF16)
     float* RX = c->f32_a;
     float* RY = c->f32_b;
     float* Yc = c->f32_c;

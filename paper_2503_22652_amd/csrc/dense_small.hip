@@ -41,7 +41,7 @@ constexpr int LDJ = JP + 1;     // padded LDS leading dimension
 // workgroup of eight waves, the matrix in LDS in 16 x 16 tiles (padded with the
 // identity).  Per tile column: wave 0 factors and inverts the 16 x 16 diagonal tile
 // in registers (lane i holds row i; the pivots and the entries of L travel by
-// readlane; 1/sqrt(d) from the hardware estimate and two Newton steps), all waves
+// readlane; 1/sqrt(d) from the hardware estimate and one step of third order), all waves
 // form the tiles below with the inverse and update the trailing tiles on
 // v_mfma_f64_16x16x4.  Then each wave forms the inverse's tiles of one tile column
 // from the top down, Linv_ij = -Linv_ii sum_k L_ik Linv_kj (the sum's accumulator has
