@@ -437,35 +437,38 @@ __global__ __launch_bounds__(256, 2) void k_step_large(StepArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// Small products: the whole step in one launch.  A workgroup forms a 32 x 32
+// Small products: the whole step in one launch.  A workgroup forms a 32 x (32 TN)
 // tile; its eight waves take the k-slices in turn (both operands packed, straight
-// from L2), add their partial tiles through LDS in wave order, and four of them
-// apply the epilogue, whose operands were requested first, and pack the next
+// from L2), add their partial tiles through LDS in wave order, and 4 TN of
+// them apply the epilogue, whose operands were requested first, and pack the next
 // step's right operand into the other of two buffers.  L2 latency and the launch bound
 // it: 1024 x 80 in FP32 takes 8.0 us a step, against 16.7 in two launches.  (More
 // slices in flight per wave change nothing.)  A branch around the use of an absent
 // operand made the compiler keep the arguments in LDS, at an address that needs the
 // dispatch packet in host memory: 14.3 us.
 // ---------------------------------------------------------------------------
-template <int P>
+template <int P, int TN>
 __global__ __launch_bounds__(512) void k_step_small(StepArgs a, int pack) {
   constexpr int NW = 8, AV = P == 1 ? 1 : 2;
-  __shared__ __attribute__((aligned(16))) f32x4 red[NW][4][64];
+  __shared__ __attribute__((aligned(16))) f32x4 red[NW][TN][4][64];
   const int t = xcd_tile(blockIdx.x, gridDim.x);
   const int n_tile = t % a.tiles_n, m_tile = t / a.tiles_n;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int l32 = lane & 31, h = lane >> 5;
-  const int n0 = n_tile * 32;
+  const int n0 = n_tile * 32 * TN;
   const char* Al = static_cast<const char*>(a.A) + int64_t(m_tile) * a.slices * (2048 * AV) + lane * 16;
   const char* Bl = reinterpret_cast<const char*>(a.Bp) + (int64_t(2 * h) * a.Np + n0 + l32) * 16;
+  // the second column half, or (past the packed columns) the first again, unused
+  const int second = n0 + 32 < a.Np ? 512 : 0;
   // this thread's part of the epilogue: four rows of one column
-  const int em = m_tile * 32 + 8 * wave + 4 * h, ec = n0 + l32, eleft = a.n - em;
-  const bool mine = wave < 4 && ec < a.N;
+  const int ew = wave & 3, et = wave >> 2;
+  const int em = m_tile * 32 + 8 * ew + 4 * h, ec = n0 + 32 * et + l32, eleft = a.n - em;
+  const bool mine = et < TN && ec < a.N;
   EpiRegs er;
   if (mine && eleft > 0) er = epi_load(a.epi, em, ec, eleft);
 
   struct Slice {
-    u32x4 x[2][AV], y[2][P];
+    u32x4 x[2][AV], y[2][TN][P];
   };
   auto load = [&](int s) __attribute__((always_inline)) {
     Slice r;
@@ -477,14 +480,19 @@ __global__ __launch_bounds__(512) void k_step_small(StepArgs a, int pack) {
       for (int i = 0; i < AV; ++i)
         r.x[u][i] = *reinterpret_cast<const u32x4*>(p + (AV * u + i) * 1024);
 #pragma unroll
-      for (int q = 0; q < P; ++q)
-        r.y[u][q] = *reinterpret_cast<const u32x4*>(b + int64_t(q * 4 + u) * 16 * a.Np);
+      for (int c = 0; c < TN; ++c)
+#pragma unroll
+        for (int q = 0; q < P; ++q)
+          r.y[u][c][q] =
+              *reinterpret_cast<const u32x4*>(b + int64_t(q * 4 + u) * 16 * a.Np + c * second);
     }
     return r;
   };
-  f32x16 acc, low;                                 // P = 3: x0 y0, and the five small terms
+  f32x16 acc[TN], low[TN];                         // P = 3: x0 y0, and the five small terms
 #pragma unroll
-  for (int i = 0; i < 16; ++i) acc[i] = low[i] = 0.f;
+  for (int c = 0; c < TN; ++c)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[c][i] = low[c][i] = 0.f;
   auto compute = [&](const Slice& r) __attribute__((always_inline)) {
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
@@ -496,11 +504,13 @@ __global__ __launch_bounds__(512) void k_step_small(StepArgs a, int pack) {
 #pragma unroll
       for (int q = P - 1; q >= 0; --q)
 #pragma unroll
-        for (int p = P - 1 - q; p >= 0; --p) {
-          f32x16& into = p + q == 0 ? acc : low;
-          into = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-              af[p], __builtin_bit_cast(bf16x8, r.y[u][q]), into, 0, 0, 0);
-        }
+        for (int p = P - 1 - q; p >= 0; --p)
+#pragma unroll
+          for (int c = 0; c < TN; ++c) {
+            f32x16& into = p + q == 0 ? acc[c] : low[c];
+            into = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                af[p], __builtin_bit_cast(bf16x8, r.y[u][c][q]), into, 0, 0, 0);
+          }
     }
   };
   // (slices past n, which fill up a segment for the large path, hold nothing)
@@ -514,17 +524,21 @@ __global__ __launch_bounds__(512) void k_step_small(StepArgs a, int pack) {
     }
     compute(cur);
   }
-  if constexpr (P == 3) acc += low;
 #pragma unroll
-  for (int g = 0; g < 4; ++g)
-    red[wave][g][lane] = f32x4{acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3]};
+  for (int c = 0; c < TN; ++c) {
+    if constexpr (P == 3) acc[c] += low[c];
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+      red[wave][c][g][lane] =
+          f32x4{acc[c][4 * g], acc[c][4 * g + 1], acc[c][4 * g + 2], acc[c][4 * g + 3]};
+  }
   __syncthreads();
   if (!mine) return;
   f32x4 v = {0.f, 0.f, 0.f, 0.f};
   if (eleft > 0) {
-    f32x4 s = red[0][wave][lane];
+    f32x4 s = red[0][et][ew][lane];
 #pragma unroll
-    for (int w = 1; w < NW; ++w) s += red[w][wave][lane];
+    for (int w = 1; w < NW; ++w) s += red[w][et][ew][lane];
     v = epi_value(a.epi, er, s, em, eleft);
     store4(a.C + em + ec * a.ldc, v, eleft);
   }
@@ -545,8 +559,11 @@ hipError_t launch_large(const StepArgs& a, int tn, hipStream_t st) {
 }
 
 template <int P>
-hipError_t launch_small(const StepArgs& a, int pack, hipStream_t st) {
-  k_step_small<P><<<dim3(unsigned(a.tiles_m) * a.tiles_n), dim3(512), 0, st>>>(a, pack);
+hipError_t launch_small(const StepArgs& a, int tn, int pack, hipStream_t st) {
+  if (tn == 2)
+    k_step_small<P, 2><<<dim3(unsigned(a.tiles_m) * a.tiles_n), dim3(512), 0, st>>>(a, pack);
+  else
+    k_step_small<P, 1><<<dim3(unsigned(a.tiles_m) * a.tiles_n), dim3(512), 0, st>>>(a, pack);
   return hipGetLastError();
 }
 
@@ -669,12 +686,19 @@ hipError_t filter_product(const FilterProduct& d, hipStream_t st, const Workspac
   a.Bp = reinterpret_cast<unsigned short*>(buf[from]);
   a.Bn = reinterpret_cast<unsigned short*>(buf[1 - from]);
   a.tiles_m = (a.n + 31) / 32;
-  a.tiles_n = (a.N + 31) / 32;
+  // Two column tiles a workgroup (the operator is split once for both) where that and not
+  // one leaves at most a workgroup to each CU.  Measured, us a step, one / two: FP32
+  // 2048 x 144 19.9 / 17.7, 3001 x 128 27.0 / 23.3, complex 1500 x 300 30.1 / 25.5, BF16
+  // 8192 x 64 27.6 / 24.6; FP32 1024 x 160 (160 tiles) 8.5 / 10.9, 4096 x 64 (256) 20.1 /
+  // 28.6, 2500 x 200 (553, in pairs 316) 34.0 / 37.5.
+  auto tiles_of = [&](int tn) { return int64_t(a.tiles_m) * ((a.N + 32 * tn - 1) / (32 * tn)); };
+  const int small_tn = tiles_of(1) > 256 && tiles_of(2) <= 256 ? 2 : 1;
+  a.tiles_n = (a.N + 32 * small_tn - 1) / (32 * small_tn);
   a.splits = 1;
   a.spc = a.slices;
   if (int64_t(a.tiles_m) * a.tiles_n > 0x7fffffff) return hipErrorInvalidValue;
   *packed = pack ? 2 - from : 0;
-  return d.planes == 3 ? launch_small<3>(a, pack, st) : launch_small<1>(a, pack, st);
+  return d.planes == 3 ? launch_small<3>(a, small_tn, pack, st) : launch_small<1>(a, small_tn, pack, st);
 }
 
 }  // namespace chfsi

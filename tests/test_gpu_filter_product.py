@@ -105,3 +105,11 @@ def test_filter_product_edges_two_launches(monkeypatch, prec, cplx, splits, n, b
 def test_filter_product_large_by_rule(prec, n, b):
     """Past the size from which a step is two launches."""
     test_filter_product_edges(prec, False, n, b)
+
+
+@pytest.mark.parametrize("n,b,cplx", [(1893, 157, False), (1893, 80, True), (2090, 127, False)])
+@pytest.mark.parametrize("prec", [P.PREC_FP32, P.PREC_BF16])
+def test_filter_product_two_column_tiles(prec, n, b, cplx):
+    """One launch with two column tiles a workgroup: a last pair whose second tile lies
+    past the packed columns (160 of 192), and one that ends at them."""
+    test_filter_product_edges(prec, cplx, n, b)
